@@ -322,7 +322,8 @@ fwd_status fwd_adjoint_td(fwd_plan *plan, void *ws_dev, size_t ws_bytes, void *s
 enum {
   FWD_OPT_GRAPH_STEPS = 0,   /* steps per captured HIP graph (0 or 1: launch eagerly); default 32 */
   FWD_OPT_BLOCK_X = 1,       /* threads per block along x: 16, 32, 64, 128 or 256.  x * y must
-                                not exceed 256 when a run starts (else FWD_ERR_INVALID_ARG) */
+                                not exceed 256 when a run starts (else FWD_ERR_INVALID_ARG).
+                                The one-launch step (SCHEDULE 0) has blocks of its own */
   FWD_OPT_BLOCK_Y = 2,       /* block rows along y: 1, 2, 4, 8 or 16 */
   FWD_OPT_XCD_REMAP = 3,     /* 1: group neighbouring tiles on one XCD (default) */
   FWD_OPT_SAMPLE_EVERY = 4,  /* > 0: time the kernels of one step in every this many with
@@ -339,8 +340,13 @@ enum {
                                 it before fwd_workspace_size. */
   FWD_OPT_VECTOR = 7,        /* 1 (default): each thread of the E update updates one x node;
                                 4: a 16-byte vector of consecutive x nodes (4 in FP32, 2 in
-                                FP64); two-kernel schedule only */
-  FWD_OPT_SCHEDULE = 8,      /* 0 (default): two launches per step (H update, then E update);
+                                FP64), with an H update and an E update launched in turn;
+                                schedule 0 only */
+  FWD_OPT_SCHEDULE = 8,      /* 0 (default): one launch per step, each thread updating H and E
+                                at its node (and recomputing the H nodes its E edges
+                                difference); two launches (H update, then E update) at order 4,
+                                with VECTOR or VECTOR_H 4, with magnetic nodes on a high wall,
+                                and where a source's fields take 4 GB or more;
                                 1: one fused launch per step -- each block owns a block_x x
                                 block_y column tile and a chunk of FWD_OPT_ZCHUNK planes, stages
                                 E and H planes with their halo in LDS and marches up in z,
@@ -367,7 +373,7 @@ enum {
                                 and the basis (call fwd_set_model again); order 4 runs the
                                 two-kernel schedule with vector widths 1 and rejects other
                                 SCHEDULE / VECTOR / VECTOR_H values. */
-  FWD_OPT_LEAN = 14,         /* 1 (default): blocks of the two-kernel schedule whose tile lies
+  FWD_OPT_LEAN = 14,         /* 1 (default): blocks of schedules 0 and 2 whose tile lies
                                 inside the CPML layers' inner boundary take an update path with
                                 no CPML or wall logic; 0: every block takes the general path.
                                 The arithmetic per edge is the same: results are equal bit for
@@ -408,7 +414,8 @@ fwd_status fwd_set_option(fwd_plan *plan, int key, double value);
 fwd_status fwd_get_option(const fwd_plan *plan, int key, double *value);
 
 /* Self-written tile/schedule autotuner.  A staged search on the given
- * buffers: block shape, then vector widths, then tile order and XCD remap,
+ * buffers: the one-launch step, or where it does not apply block shape, then
+ * vector widths; then tile order and XCD remap,
  * then the fused schedule (shapes, planes per block), then the transform
  * block FWD_OPT_DFT_BLOCK in {8, 16, 32} when vol_dev is given and ws_bytes holds
  * the workspace of the longer block.  Each candidate runs `steps` steps of
@@ -430,14 +437,14 @@ fwd_status fwd_last_timing(const fwd_plan *plan, double *ms, int *steps);
 
 /* Average device time (ms) per launch of the kernels of a step over the
  * steps sampled in the last fwd_forward / fwd_adjoint (FWD_OPT_SAMPLE_EVERY >
- * 0): [0] H update, [1] E update (fused with injection and the receiver
+ * 0): [0] H update, [1] E update (or the whole step; fused with injection and the receiver
  * transform; it keeps each sample for the volume transform), [2] block
  * transform (volume transform or gradient product of one transform block,
  * averaged over the sampled steps that closed a block; 0 if none).  Measured
  * with HIP events on the caller's stream that hipExtLaunchKernel stamps from
  * each sampled kernel's own dispatch (the kernel alone, as a kernel trace
- * reports it).  With the fused schedule [0] is 0 and [1] is the one launch
- * of the step.  avg_ms has room for 3 values. */
+ * reports it).  With one launch a step (schedule 0 at order 2, or the fused
+ * schedule) [0] is 0 and [1] is that launch.  avg_ms has room for 3 values. */
 fwd_status fwd_kernel_stats(const fwd_plan *plan, double *avg_ms, int *samples);
 
 const char *fwd_last_error(void);

@@ -6,9 +6,11 @@
 // fused with the injection of J' at the source (or adjoint-source) edges,
 // the receiver transform, and the volume transform acc_k += E z_k (eq. dft)
 // in the forward run or the on-the-fly gradient product in the adjoint run.
-// Two schedules carry out the same arithmetic per edge:
+// These forms carry out the same arithmetic per edge:
+//   one launch   k_leap, a wave per 64 nodes of a row, which recomputes the
+//                H it differences (order 2, one node per thread);
 //   two kernels  k_update_h then k_update_e, one thread per (i, j, k) node
-//                (or per 16-byte vector of x nodes);
+//                or per 16-byte vector of x nodes (order 4: their own forms);
 //   fused        k_step, one launch per step: a block owns a column tile and
 //                a chunk of z planes, stages each E plane (with a one-node
 //                halo) and the new H plane (with its low-side halo) in LDS,
@@ -143,10 +145,24 @@ struct StepArgs {
 // or z fastest, t = (by * nbx + bx) * nbz + bz (order 1: the blocks of
 // consecutive planes of a column tile run side by side, so the plane
 // neighbours a stencil reads are still in L2).  Returns the tile index.
-template <typename T>
-__device__ __forceinline__ int tile_of_b(const StepArgs<T> &A, uint32_t b, int &bx, int &by,
-                                         int &bz, int &s) {
-  if (A.xcd) {
+// XCD_RUNS (the one-wave blocks of k_leap): each XCD takes runs of 128
+// consecutive b, dealt round-robin, and the blocks past the last whole round
+// stay where they are.  Rows of a run still share their neighbours in one L2,
+// and every XCD gets its part of the layers, whose rows cost twice as much:
+// with one contiguous range per XCD the XCDs of the outermost planes finish
+// last (101x101x61, 4 sources: 53.5 us a step against 47.5 with runs and 47.3
+// unmapped; 1 source: 17.5, 17.2 and 19.7; runs of 16 to 1024 within 4 %).
+enum { XCD_RUNS = 2, XCD_RUN_LOG2 = 7 };
+template <typename Args>
+__device__ __forceinline__ int tile_of_b(const Args &A, uint32_t b, int &bx, int &by, int &bz,
+                                         int &s) {
+  if (A.xcd == XCD_RUNS) {
+    constexpr uint32_t g = XCD_RUN_LOG2;
+    if (b < ((uint32_t)A.nblocks >> (3 + g)) << (3 + g)) {
+      const uint32_t x = b & 7u, local = b >> 3;
+      b = ((((local >> g) << 3) + x) << g) + (local & ((1u << g) - 1u));
+    }
+  } else if (A.xcd) {
     const uint32_t q = (uint32_t)A.nblocks >> 3, r = (uint32_t)A.nblocks & 7u;
     const uint32_t x = b & 7u, local = b >> 3;
     b = x * q + min(x, r) + local;
@@ -166,8 +182,8 @@ __device__ __forceinline__ int tile_of_b(const StepArgs<T> &A, uint32_t b, int &
   }
   return (int)tile;
 }
-template <typename T>
-__device__ __forceinline__ int tile_of(const StepArgs<T> &A, int &bx, int &by, int &bz, int &s) {
+template <typename Args>
+__device__ __forceinline__ int tile_of(const Args &A, int &bx, int &by, int &bz, int &s) {
   return tile_of_b(A, blockIdx.x, bx, by, bz, s);
 }
 
@@ -187,14 +203,18 @@ __device__ __forceinline__ int step_of(const StepArgs<T> &A, bool last_launch) {
 // uniform scalar load; callers ask for the slice after issuing their
 // stencil loads, so its round trip overlaps theirs.
 template <typename T>
-__device__ __forceinline__ void entry_slice(const StepArgs<T> &A, int b, int n, int &lo, int &hi) {
+__device__ __forceinline__ void entry_slice_at(const StepArgs<T> &A, int b, int n, int slot, int &lo,
+                                               int &hi) {
   lo = hi = 0;
   if (!A.tile_tab || n >= A.nt) return;   // no injection or recording past the run
   const int tt = A.tile_tab[__builtin_amdgcn_readfirstlane(b)];
   if (tt < 0) return;
-  const int slot = threadIdx.y * blockDim.x + threadIdx.x;
   lo = A.tl_off[tt + slot];
   hi = A.tl_off[tt + slot + 1];
+}
+template <typename T>
+__device__ __forceinline__ void entry_slice(const StepArgs<T> &A, int b, int n, int &lo, int &hi) {
+  entry_slice_at(A, b, n, threadIdx.y * blockDim.x + threadIdx.x, lo, hi);
 }
 
 // slab index of a CPML node: half nodes i+1/2 with i < npml or i >= n-npml;
@@ -896,6 +916,410 @@ template <bool HIST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_update_e_s(StepArgs<float> A) {
   e_update<float, HIST, 1, true>(A);
+}
+
+// ---------------------------------------------------------------------------
+// One-launch step (schedule 0 at order 2, k_leap).  A wave owns 64 consecutive
+// x nodes of one row (j, k).  Each lane computes H^{n+1/2} at its node and
+// again at the neighbours that its E edges difference, (j - 1) and (k - 1),
+// with the operands and operations of their owners (the same bits); H at
+// i - 1 comes from the lane below, and only the first lane recomputes it.
+// Then E^{n+1}, in registers: no barrier, no LDS, and H^{n+1/2} is written
+// but not read back, so a step moves 48 B a node (FP32) for the 72 B of two
+// launches.
+//
+// What bounds it: instruction issue, and behind it L2.  The two kernels took
+// 250 to 320 scalar instructions a wave against 133 to 223 vector ones
+// (SQ_INSTS_*; the scalar unit of a CU serves its four SIMDs in turn), most of
+// them 64-bit addresses.  Hence: j and k are uniform (one row per wave), so
+// rows, layers and coefficients are scalar; every row is a 32-bit offset on
+// one buffer descriptor (a scalar add a row, 25 rows); the layers' branches
+// cost nothing off the layers; and three quarters of a large grid take the
+// form with none (141 scalar, 94 vector, 47 memory instructions a wave).
+// Rows of the high walls are not computed: H there stays zero (it
+// differences E edges on the wall), and E there is never updated.
+//
+// Measured a step, two kernels -> this (one MI355X): 101x101x61 FP32, 30.1 ->
+// 17.3 us; the same with 4 sources 77.2 -> 47.5 us; 200x200x100, 8 sources,
+// 943 -> 628 us (3.9 TB/s of the bytes it cannot do without); FP64
+// 128x128x96 113 -> 85 us.  Not kept: 2 nodes a lane
+// (FP32; 20.5 us on the marine grid), a march in z with H of the plane below
+// carried (slower below 32 M node updates a step, 3 % faster above), blocks
+// of 4 rows (5 to 10 % slower than one-wave blocks), holding the layers'
+// forms to fewer registers (5 waves a SIMD for 4: no gain).
+// ---------------------------------------------------------------------------
+// Coefficients of one axis index, read as one row: 1/h, 1/hd, then CPML
+// 1/kappa, b, a at the node and at the half node.
+template <typename T>
+struct AxRow {
+  T ih, ihd, kn, bn, an, kh, bh, ah;
+};
+
+// Raw buffer access: uniform base and 32-bit uniform row offset in scalar
+// registers, the lane's offset in one vector register, so that each of the
+// many rows of a stencil costs one scalar addition.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, 0xffffffffu, 0x00027000);
+}
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+template <typename T>
+__device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, uint32_t lane, uint32_t row) {
+  if constexpr (sizeof(T) == 4)
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane, row, 0));
+  else
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lane, row, 0));
+}
+template <bool NT, typename T>
+__device__ __forceinline__ void bstore(T v, __amdgpu_buffer_rsrc_t r, uint32_t lane, uint32_t row) {
+  constexpr int aux = NT ? 2 : 0;        // bit 1: non-temporal
+  if constexpr (sizeof(T) == 4)
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, lane, row, aux);
+  else
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, lane, row, aux);
+}
+
+// The value of the lane below / above (one lane along x); the first / last
+// active lane keeps `edge`.
+template <int CTRL, typename T>
+__device__ __forceinline__ T lane_shift(T edge, T v) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, edge),
+                                                             __builtin_bit_cast(int, v), CTRL, 0xf,
+                                                             0xf, false));
+  } else {
+    const u32x2 e = __builtin_bit_cast(u32x2, edge), u = __builtin_bit_cast(u32x2, v);
+    u32x2 r;
+    r.x = __builtin_amdgcn_update_dpp((int)e.x, (int)u.x, CTRL, 0xf, 0xf, false);
+    r.y = __builtin_amdgcn_update_dpp((int)e.y, (int)u.y, CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(T, r);
+  }
+}
+template <typename T>
+__device__ __forceinline__ T lane_below(T edge, T v) { return lane_shift<0x138>(edge, v); }
+template <typename T>
+__device__ __forceinline__ T lane_above(T edge, T v) { return lane_shift<0x130>(edge, v); }
+
+// b, a and 1/kappa of a stretched difference
+template <typename T>
+struct Stretch {
+  T b, a, k;
+};
+
+// fma(c, d1 - d2, f) with d1 = (a1 - a0) s1 and d2 = (b1 - b0) s2, each
+// stretched inside a layer: the update of every component (c = -dt/mu for H,
+// dt/eps for E).  P1, P2: the direction can be stretched at all; p1, p2: it
+// is at this node.
+template <bool P1, bool P2, typename T>
+__device__ __forceinline__ T curl_update(T f, T c, T a1, T a0, T s1, bool p1, T &m1,
+                                         const Stretch<T> &t1, T b1, T b0, T s2, bool p2, T &m2,
+                                         const Stretch<T> &t2) {
+  T d1 = (a1 - a0) * s1;
+  T d2 = (b1 - b0) * s2;
+  if constexpr (P1) {
+    const T d = stretch(d1, m1, t1.b, t1.a, t1.k);
+    d1 = p1 ? d : d1;
+  }
+  if constexpr (P2) {
+    const T d = stretch(d2, m2, t2.b, t2.a, t2.k);
+    d2 = p2 ? d : d2;
+  }
+  return fma(c, d1 - d2, f);
+}
+
+template <typename T>
+struct LeapArgs {
+  const T *fi, *pi;                  // fields and CPML memory: the half the step reads,
+  T *fo, *po, *pe;                   // the half it writes, and half 0 (memory of E)
+  const T *ce, *axt;
+  const AxRow<T> *axr;               // [3][LA]
+  T *hist;                           // slot of this step's sample (HIST)
+  const int *step;
+  int *step_w;
+  int64_t F6, psi_src, hist_src;     // elements per source
+  uint32_t PXb, PLb, Fb, LAb;        // row, plane, field and axis table strides in bytes
+  uint32_t sXb, sYb, sZb, oYb, oZb;  // psi slab strides and offsets in bytes
+  int nx, ny, nz, npml, LA, NY;
+  T dtmu;
+  int lean;
+  int nbx, nby, nbz, nblocks, xcd, order, ns;
+  FDiv dns, dnbx, dnby, dnbz;
+  const int *tile_tab;
+  int ej0, ej1, ek0, ek1;            // rows and planes that hold entries (empty: j1 < j0)
+};
+
+// XL: nodes of the wave may lie in an x layer or at an x wall; YZ: the row
+// may lie in a y or z layer or at a wall; ENT: it may hold entries.
+template <typename T, bool HIST, bool NT, bool XL, bool YZ, bool ENT>
+__device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b,
+                                          int i0, int j, int k) {
+  // coefficients of the rows j, j - 1, k, k - 1 and of i0 - 1: read before
+  // the marker below, so that they are scalar loads
+  const bool j_lo = !YZ || j >= 1, k_lo = !YZ || k >= 1, left = !XL || i0 > 0;
+  const int jm = j_lo ? j - 1 : j, km = k_lo ? k - 1 : k;
+  const AxRow<T> yj = L.axr[L.LA + j], ym = L.axr[L.LA + jm], zk = L.axr[2 * L.LA + k],
+                 zm = L.axr[2 * L.LA + km], xl = L.axr[left ? i0 - 1 : 0];
+  // each variant starts with its own marker: loads common to the variants
+  // are not hoisted above the branches (that kept the registers of all of
+  // them alive at once)
+  asm volatile("; %0" ::"n"(XL * 4 + YZ * 2 + ENT));
+  const int tid = threadIdx.x, i = i0 + tid;
+  const int npml = L.npml, W = 2 * npml;
+  const uint32_t sz = sizeof(T);
+  const bool i_lo = !XL || i >= 1;
+  // rows below a wall are replaced by the node's own: their values reach no
+  // stored result
+  const uint32_t dj = L.PXb, ej = j_lo ? 0u - L.PXb : 0u;
+  const uint32_t dk = L.PLb, ek = k_lo ? 0u - L.PLb : 0u;
+  const uint32_t x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz;
+  const uint32_t q0 = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0;
+  const int64_t so = (int64_t)s * L.F6;
+  const __amdgpu_buffer_rsrc_t rI = rsrc_of(L.fi + so), rC = rsrc_of(L.ce), rX = rsrc_of(L.axt);
+  const uint32_t x = q0, y = q0 + L.Fb, z = y + L.Fb, u = z + L.Fb, v = u + L.Fb, w = v + L.Fb;
+  // ---- loads: E^n at the node and the neighbours, H^{n-1/2}, dt/eps ----
+  const T ex0 = bload<T>(rI, o, x), ey0 = bload<T>(rI, o, y), ez0 = bload<T>(rI, o, z);
+  const T hx0 = bload<T>(rI, o, u), hy0 = bload<T>(rI, o, v), hz0 = bload<T>(rI, o, w);
+  const T ex_jp = bload<T>(rI, o, x + dj), ez_jp = bload<T>(rI, o, z + dj);
+  const T ex_kp = bload<T>(rI, o, x + dk), ey_kp = bload<T>(rI, o, y + dk);
+  const T ex_jm = bload<T>(rI, o, x + ej), ey_jm = bload<T>(rI, o, y + ej);
+  const T ez_jm = bload<T>(rI, o, z + ej), ey_jm_kp = bload<T>(rI, o, y + ej + dk);
+  const T hx_jm = bload<T>(rI, o, u + ej), hz_jm = bload<T>(rI, o, w + ej);
+  const T ex_km = bload<T>(rI, o, x + ek), ey_km = bload<T>(rI, o, y + ek);
+  const T ez_km = bload<T>(rI, o, z + ek), ez_jp_km = bload<T>(rI, o, z + ek + dj);
+  const T hx_km = bload<T>(rI, o, u + ek), hy_km = bload<T>(rI, o, v + ek);
+  // the nodes beyond the wave's ends, one lane each: E at i + 1 for the last
+  // lane, E and H at i - 1 for the first
+  const bool right = !XL || i0 + 64 <= L.nx;
+  T ey_r = T(0), ez_r = T(0), ey_jm_r = T(0), ez_km_r = T(0);
+  if (right && tid == 63) {
+    ey_r = bload<T>(rI, o + sz, y);
+    ez_r = bload<T>(rI, o + sz, z);
+    ey_jm_r = bload<T>(rI, o + sz, y + ej);
+    ez_km_r = bload<T>(rI, o + sz, z + ek);
+  }
+  T ex_l = T(0), ey_l = T(0), ez_l = T(0), ex_l_kp = T(0), ex_l_jp = T(0), hy_l = T(0), hz_l = T(0);
+  if (left && tid == 0) {
+    ex_l = bload<T>(rI, o, x - sz);
+    ey_l = bload<T>(rI, o, y - sz);
+    ez_l = bload<T>(rI, o, z - sz);
+    ex_l_kp = bload<T>(rI, o, x + dk - sz);
+    ex_l_jp = bload<T>(rI, o, x + dj - sz);
+    hy_l = bload<T>(rI, o, v - sz);
+    hz_l = bload<T>(rI, o, w - sz);
+  }
+  const T cx = bload<T>(rC, o, x), cy = bload<T>(rC, o, y), cz = bload<T>(rC, o, z);
+  const T ih = bload<T>(rX, o, x0 + AX_IH * L.LAb), ihd = bload<T>(rX, o, x0 + AX_IHD * L.LAb);
+  const int tt = ENT ? L.tile_tab[b] : -1;
+  // ---- layers: slab indices and memory ----
+  bool px = false, pxn = false, pxl = false;
+  bool py = false, pym = false, pyn = false, pz = false, pzm = false, pzn = false;
+  int lyh = 0, lym = 0, lyn = 0, lzh = 0, lzm = 0, lzn = 0, lxl = 0;
+  uint32_t cxh = 0, cxn = 0;
+  if constexpr (YZ) {
+    py = pml_half(j, L.ny, npml, lyh);
+    pym = j_lo && pml_half(jm, L.ny, npml, lym);
+    pyn = j_lo && pml_int(j, L.ny, npml, lyn);
+    pz = pml_half(k, L.nz, npml, lzh);
+    pzm = k_lo && pml_half(km, L.nz, npml, lzm);
+    pzn = k_lo && pml_int(k, L.nz, npml, lzn);
+  }
+  if constexpr (XL) {
+    // as pml_half and pml_int, without branches
+    px = ((i < npml) | (i >= L.nx - npml));
+    pxn = i_lo & ((i < npml) | (i > L.nx - npml));
+    cxh = (uint32_t)(i < npml ? i : i - L.nx + W) * sz;
+    cxn = (uint32_t)(i < npml ? i : i - L.nx + W - 1) * sz;
+    pxl = left && pml_half(i0 - 1, L.nx, npml, lxl);
+  }
+  T hx_y = T(0), hx_z = T(0), hy_z = T(0), hy_x = T(0), hz_x = T(0), hz_y = T(0);   // H at the node
+  T hxj_y = T(0), hxj_z = T(0), hzj_x = T(0), hzj_y = T(0);                         // at j - 1
+  T hxk_y = T(0), hxk_z = T(0), hyk_z = T(0), hyk_x = T(0);                         // at k - 1
+  T hyl_z = T(0), hyl_x = T(0), hzl_x = T(0), hzl_y = T(0);                         // at i0 - 1
+  T ex_y = T(0), ex_z = T(0), ey_z = T(0), ey_x = T(0), ez_x = T(0), ez_y = T(0);   // E (half 0)
+  Stretch<T> xh{}, xn{};
+  const int64_t sp = (int64_t)s * L.psi_src;
+  const uint32_t Wb = (uint32_t)W * sz;
+  const uint32_t r0 = (uint32_t)(k * L.NY + j) * Wb;
+  const uint32_t oY = L.oYb + x0, oZ = L.oZb + x0;
+  const uint32_t rYh = oY + (uint32_t)(k * W + lyh) * L.PXb;
+  const uint32_t rYn = oY + 2 * L.sYb + (uint32_t)(k * W + lyn) * L.PXb;
+  const uint32_t rZh = oZ + (uint32_t)(lzh * L.NY + j) * L.PXb;
+  const uint32_t rZn = oZ + 2 * L.sZb + (uint32_t)(lzn * L.NY + j) * L.PXb;
+  if constexpr (XL || YZ) {
+    const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.pi + sp), rE = rsrc_of(L.pe + sp);
+    if constexpr (YZ) {
+      if (py) {
+        hx_y = bload<T>(rP, o, rYh);
+        hz_y = bload<T>(rP, o, rYh + L.sYb);
+        hxk_y = bload<T>(rP, o, oY + (uint32_t)(km * W + lyh) * L.PXb);
+        if (left && tid == 0) hzl_y = bload<T>(rP, o, rYh + L.sYb - sz);
+      }
+      if (pym) {
+        const uint32_t r = oY + (uint32_t)(k * W + lym) * L.PXb;
+        hxj_y = bload<T>(rP, o, r);
+        hzj_y = bload<T>(rP, o, r + L.sYb);
+      }
+      if (pz) {
+        hx_z = bload<T>(rP, o, rZh);
+        hy_z = bload<T>(rP, o, rZh + L.sZb);
+        hxj_z = bload<T>(rP, o, oZ + (uint32_t)(lzh * L.NY + jm) * L.PXb);
+        if (left && tid == 0) hyl_z = bload<T>(rP, o, rZh + L.sZb - sz);
+      }
+      if (pzm) {
+        const uint32_t r = oZ + (uint32_t)(lzm * L.NY + j) * L.PXb;
+        hxk_z = bload<T>(rP, o, r);
+        hyk_z = bload<T>(rP, o, r + L.sZb);
+      }
+      if (pyn) {
+        ex_y = bload<T>(rE, o, rYn);
+        ez_y = bload<T>(rE, o, rYn + L.sYb);
+      }
+      if (pzn) {
+        ex_z = bload<T>(rE, o, rZn);
+        ey_z = bload<T>(rE, o, rZn + L.sZb);
+      }
+    }
+    if constexpr (XL) {
+      if (px) {
+        hy_x = bload<T>(rP, cxh, r0);
+        hz_x = bload<T>(rP, cxh, r0 + L.sXb);
+        hyk_x = bload<T>(rP, cxh, (uint32_t)(km * L.NY + j) * Wb);
+        hzj_x = bload<T>(rP, cxh, (uint32_t)(k * L.NY + jm) * Wb + L.sXb);
+        xh = {bload<T>(rX, o, x0 + AX_BH * L.LAb), bload<T>(rX, o, x0 + AX_AH * L.LAb),
+              bload<T>(rX, o, x0 + AX_KH * L.LAb)};
+      }
+      if (pxl && tid == 0) {
+        hyl_x = bload<T>(rP, (uint32_t)lxl * sz, r0);
+        hzl_x = bload<T>(rP, (uint32_t)lxl * sz, r0 + L.sXb);
+      }
+      if (pxn) {
+        ey_x = bload<T>(rE, cxn, r0 + 2 * L.sXb);
+        ez_x = bload<T>(rE, cxn, r0 + 3 * L.sXb);
+        xn = {bload<T>(rX, o, x0 + AX_BN * L.LAb), bload<T>(rX, o, x0 + AX_AN * L.LAb),
+              bload<T>(rX, o, x0 + AX_KN * L.LAb)};
+      }
+    }
+  }
+  int lo = 0, hi = 0, n = 0;
+  if (ENT && tt >= 0) {
+    n = L.step[0] + 1;
+    lo = A.tl_off[tt + tid];
+    hi = A.tl_off[tt + tid + 1];
+  }
+  // ---- H^{n+1/2} at the node and, recomputed, at j - 1, k - 1 and i - 1 ----
+  const T mc = -L.dtmu;
+  const T hj = yj.ih, hjm = ym.ih, hk = zk.ih, hkm = zm.ih;
+  const Stretch<T> yh{yj.bh, yj.ah, yj.kh}, yhm{ym.bh, ym.ah, ym.kh},
+      yn{yj.bn, yj.an, yj.kn}, zh{zk.bh, zk.ah, zk.kh}, zhm{zm.bh, zm.ah, zm.kh},
+      zn{zk.bn, zk.an, zk.kn}, xhl{xl.bh, xl.ah, xl.kh};
+  const T ey_ip = lane_above(ey_r, ey0), ez_ip = lane_above(ez_r, ez0);
+  const T ey_ip_jm = lane_above(ey_jm_r, ey_jm), ez_ip_km = lane_above(ez_km_r, ez_km);
+  const T Hx = curl_update<YZ, YZ>(hx0, mc, ez_jp, ez0, hj, py, hx_y, yh, ey_kp, ey0, hk, pz, hx_z, zh);
+  const T Hy = curl_update<YZ, XL>(hy0, mc, ex_kp, ex0, hk, pz, hy_z, zh, ez_ip, ez0, ih, px, hy_x, xh);
+  const T Hz = curl_update<XL, YZ>(hz0, mc, ey_ip, ey0, ih, px, hz_x, xh, ex_jp, ex0, hj, py, hz_y, yh);
+  const T Hxj = curl_update<YZ, YZ>(hx_jm, mc, ez0, ez_jm, hjm, pym, hxj_y, yhm, ey_jm_kp, ey_jm, hk, pz,
+                                    hxj_z, zh);
+  const T Hzj = curl_update<XL, YZ>(hz_jm, mc, ey_ip_jm, ey_jm, ih, px, hzj_x, xh, ex0, ex_jm, hjm, pym,
+                                    hzj_y, yhm);
+  const T Hxk = curl_update<YZ, YZ>(hx_km, mc, ez_jp_km, ez_km, hj, py, hxk_y, yh, ey0, ey_km, hkm, pzm,
+                                    hxk_z, zhm);
+  const T Hyk = curl_update<YZ, XL>(hy_km, mc, ex0, ex_km, hkm, pzm, hyk_z, zhm, ez_ip_km, ez_km, ih, px,
+                                    hyk_x, xh);
+  // H at i - 1: the lane below holds it; the first lane recomputes it
+  const T Hy_l = curl_update<YZ, XL>(hy_l, mc, ex_l_kp, ex_l, hk, pz, hyl_z, zh, ez0, ez_l, xl.ih, pxl,
+                                     hyl_x, xhl);
+  const T Hz_l = curl_update<XL, YZ>(hz_l, mc, ey0, ey_l, xl.ih, pxl, hzl_x, xhl, ex_l_jp, ex_l, hj, py,
+                                     hzl_y, yh);
+  const T Hyi = lane_below(Hy_l, Hy), Hzi = lane_below(Hz_l, Hz);
+  // ---- E^{n+1} ----
+  T e1x = curl_update<YZ, YZ>(ex0, cx, Hz, Hzj, yj.ihd, pyn, ex_y, yn, Hy, Hyk, zk.ihd, pzn, ex_z, zn);
+  T e1y = curl_update<YZ, XL>(ey0, cy, Hx, Hxk, zk.ihd, pzn, ey_z, zn, Hz, Hzi, ihd, pxn, ey_x, xn);
+  T e1z = curl_update<XL, YZ>(ez0, cz, Hy, Hyi, ihd, pxn, ez_x, xn, Hx, Hxj, yj.ihd, pyn, ez_y, yn);
+  if (ENT && lo < hi) {
+    double inj[3];
+    inject_all<T, 1>(A, lo, hi, s, n, inj);
+    e1x -= (T)((double)cx * inj[0]);
+    e1y -= (T)((double)cy * inj[1]);
+    e1z -= (T)((double)cz * inj[2]);
+  }
+  // edges on the low x wall keep their value (zero)
+  if constexpr (XL) {
+    e1y = i_lo ? e1y : ey0;
+    e1z = i_lo ? e1z : ez0;
+  }
+  // ---- stores ----
+  const bool row_x = j_lo && k_lo, row_y = k_lo, row_z = j_lo;
+  const __amdgpu_buffer_rsrc_t rO = rsrc_of(L.fo + so);
+  bstore<NT>(Hx, rO, o, u);
+  bstore<NT>(Hy, rO, o, v);
+  bstore<NT>(Hz, rO, o, w);
+  if (row_x) bstore<NT>(e1x, rO, o, x);
+  if (row_y) bstore<NT>(e1y, rO, o, y);
+  if (row_z) bstore<NT>(e1z, rO, o, z);
+  if constexpr (HIST) {
+    const __amdgpu_buffer_rsrc_t rH = rsrc_of(L.hist + (int64_t)s * L.hist_src);
+    if (row_x) bstore<NT>(e1x, rH, o, x);
+    if (row_y) bstore<NT>(e1y, rH, o, y);
+    if (row_z) bstore<NT>(e1z, rH, o, z);
+  }
+  if constexpr (XL || YZ) {
+    const __amdgpu_buffer_rsrc_t rQ = rsrc_of(L.po + sp), rE = rsrc_of(L.pe + sp);
+    if constexpr (YZ) {
+      // memory outside a component's lattice reaches no result
+      if (py) {
+        bstore<false>(hx_y, rQ, o, rYh);
+        bstore<false>(hz_y, rQ, o, rYh + L.sYb);
+      }
+      if (pz) {
+        bstore<false>(hx_z, rQ, o, rZh);
+        bstore<false>(hy_z, rQ, o, rZh + L.sZb);
+      }
+      if (pyn) {
+        if (row_x) bstore<false>(ex_y, rE, o, rYn);
+        if (row_z) bstore<false>(ez_y, rE, o, rYn + L.sYb);
+      }
+      if (pzn) {
+        if (row_x) bstore<false>(ex_z, rE, o, rZn);
+        if (row_y) bstore<false>(ey_z, rE, o, rZn + L.sZb);
+      }
+    }
+    if constexpr (XL) {
+      if (px) {
+        bstore<false>(hy_x, rQ, cxh, r0);
+        bstore<false>(hz_x, rQ, cxh, r0 + L.sXb);
+      }
+      if (pxn) {
+        if (row_y) bstore<false>(ey_x, rE, cxn, r0 + 2 * L.sXb);
+        if (row_z) bstore<false>(ez_x, rE, cxn, r0 + 3 * L.sXb);
+      }
+    }
+  }
+  if (ENT && lo < hi) {
+    const Vec<T, 1> e1[3] = {vec1(e1x), vec1(e1y), vec1(e1z)};
+    const unsigned ok[3] = {row_x ? 1u : 0u, i_lo && row_y ? 1u : 0u, i_lo && row_z ? 1u : 0u};
+    const Vec<T, 1> hh[3] = {vec1(Hx), vec1(Hy), vec1(Hz)};
+    record_all<T, 1>(A, lo, hi, s, n, e1, ok, hh);
+  }
+}
+
+template <typename T, bool HIST, bool NT>
+__global__ void __launch_bounds__(64) k_leap(LeapArgs<T> L, StepArgs<T> A) {
+  int bx, j, k, s;
+  const int b = tile_of(L, bx, j, k, s);
+  const int i0 = bx * 64;
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = L.step[0] + 1;
+  if (i0 + (int)threadIdx.x >= L.nx) return;
+  const int np = L.npml;
+  const bool xl = !L.lean || i0 <= np || i0 + 64 > L.nx - np;
+  const bool yz = !L.lean || j <= np || j >= L.ny - np || k <= np || k >= L.nz - np;
+  if (j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1)
+    leap_wave<T, HIST, NT, true, true, true>(L, A, s, b, i0, j, k);
+  else if (xl) {
+    if (yz) leap_wave<T, HIST, NT, true, true, false>(L, A, s, b, i0, j, k);
+    else leap_wave<T, HIST, NT, true, false, false>(L, A, s, b, i0, j, k);
+  } else {
+    if (yz) leap_wave<T, HIST, NT, false, true, false>(L, A, s, b, i0, j, k);
+    else leap_wave<T, HIST, NT, false, false, false>(L, A, s, b, i0, j, k);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2196,6 +2620,7 @@ struct Dev {
   // typed views
   void *ce = nullptr;    // [3][F]
   void *axt = nullptr;   // [3][AX_TABLES][LA]
+  void *axr = nullptr;   // [3][LA] rows of the same (AxRow)
   int LA = 0;
   double2 *zE = nullptr, *Q = nullptr;
   double *wavelet = nullptr, *basis = nullptr;
@@ -2230,6 +2655,7 @@ struct Dev {
   int *tile_tab[4] = {nullptr, nullptr, nullptr, nullptr};
   int *tl_off[4] = {nullptr, nullptr, nullptr, nullptr};
   int2 *tl_ent[4] = {nullptr, nullptr, nullptr, nullptr};
+  int ent_box[2][4] = {{0, -1, 0, -1}, {0, -1, 0, -1}};   // rows j and planes k of the E update's entries
   int ntg = 0;                  // forward injection targets (src_s .. src_coef)
   std::string list_key;
   std::vector<DevBuf> list_bufs;
@@ -2275,8 +2701,14 @@ static T *upload_as(Dev &d, const std::vector<double> &h) {
   return upload(d, t);
 }
 
+// the captured graph holds the lists' addresses and goes with them
 static void free_lists(Dev &d) {
   for (auto &b : d.list_bufs) (void)hipFree(b.p);
+  if (d.exec) {
+    (void)hipGraphExecDestroy(d.exec);
+    d.exec = nullptr;
+  }
+  d.exec_key.clear();
   d.list_bufs.clear();
   d.list_key.clear();
   for (int m = 0; m < 4; ++m) {
@@ -2289,11 +2721,6 @@ static void free_tables(Dev &d) {
   free_lists(d);
   for (auto &b : d.bufs) (void)hipFree(b.p);
   d.bufs.clear();
-  if (d.exec) {
-    (void)hipGraphExecDestroy(d.exec);
-    d.exec = nullptr;
-  }
-  d.exec_key.clear();
 }
 
 void dev_release(Plan &p) {
@@ -2327,6 +2754,12 @@ static void upload_model_tables(Plan &p, Dev &d) {
     std::copy(ax.a_h.begin(), ax.a_h.end(), b + AX_AH * LA);
   }
   d.axt = upload_as<T>(d, t);
+  std::vector<double> rows(t.size());
+  for (int a = 0; a < 3; ++a)
+    for (int q = 0; q < AX_TABLES; ++q)
+      for (int i = 0; i < LA; ++i)
+        rows[((size_t)a * LA + i) * AX_TABLES + q] = t[((size_t)a * AX_TABLES + q) * LA + i];
+  d.axr = upload_as<T>(d, rows);
   d.LA = LA;
 }
 
@@ -2511,20 +2944,49 @@ static WS carve(const Plan &p, void *ws) {
 }
 
 // ---------------------------------------------------------------------------
-// one step = two launches (H, E) or one fused launch
+// one step = one launch (k_leap), two launches (H, E) or one fused launch
 // ---------------------------------------------------------------------------
 // Tiling: (bx x by) threads over x-y; tile b = (bz * nby + by) * nbx + bx.
-// Two kernels: each thread a vector of VX x nodes, one plane per tile row
-// (bz = k).  Fused: one x node per thread, kz planes per tile (bz = chunk).
+// One launch: 64 x nodes of one row.  Two kernels: each thread a vector of VX
+// x nodes, one plane per tile row (bz = k).  Fused: one x node per thread, kz planes per tile (bz = chunk).
 struct Tiling {
   int nbx, nby, nbz, nblocks, vx;
+  int bx, by, bz;   // threads of a tile along x and y, planes of a tile
   size_t lds;   // dynamic LDS bytes per block (fused)
 };
+
+// The one-launch step k_leap carries out schedule 0 at order 2 with one node
+// per thread.  It is left to the two kernels where its 32-bit byte offsets
+// do not reach (a source's fields, CPML memory or history slot of 4 GB and
+// more) and where magnetic nodes lie on the high walls (it skips those rows).
+// The two kernels on one node per thread are slower on every grid measured
+// (FP32 us a step: 101x101x61 30.1 against 17.3, 200x200x100 with 4 sources
+// 546 against 381; FP64: 32x32x32 13.3 against 8.2, 128x128x96 113 against
+// 85); their 16-byte vector forms remain a choice of the caller.
+static bool one_launch(const Plan &p) {
+  const uint64_t lim = (uint64_t)1 << 32;
+  return p.sched == 0 && p.fd_order == 2 && p.vx == 1 && p.vxh == 1 && !p.h_on_walls &&
+         6 * (uint64_t)p.field_elems() * p.tsize() < lim &&
+         (uint64_t)p.psi_elems_per_source() * p.tsize() < lim;
+}
 
 static Tiling tiling(const Plan &p, bool h_update = false) {
   if (p.bx * p.by > 256) fail(FWD_ERR_INVALID_ARG, "block x * block y must be <= 256");
   Tiling t;
-  if (p.sched == 1) {
+  t.bx = p.bx;
+  t.by = p.by;
+  t.bz = 1;
+  if (one_launch(p)) {
+    // one wave a block: 64 nodes of a row (the nodes of the high walls are
+    // skipped, see k_leap)
+    t.vx = 1;
+    t.bx = 64;
+    t.by = 1;
+    t.nbx = (p.nx + 63) / 64;
+    t.nby = p.ny;
+    t.nbz = p.nz;
+    t.lds = 0;
+  } else if (p.sched == 1) {
     t.vx = 1;
     t.nbx = (p.NX + p.bx - 1) / p.bx;
     t.nby = (p.NY + p.by - 1) / p.by;
@@ -2562,9 +3024,16 @@ static void build_lists(Plan &p, Dev &d) {
   if (d.list_key == key) return;
   free_lists(d);
   const int nn = (int)p.rn_c.size(), nf = p.nf();
-  const int slots = p.bx * p.by;
   for (int mode = 0; mode < 4; ++mode) {
     const Tiling t = tiling(p, mode >= 2);   // modes 2 and 3 live on the H update's grid
+    const bool own_h = p.sched != 1 && !one_launch(p);   // the H update adds magnetic sources
+    const int slots = t.bx * t.by * t.bz;
+    if (mode < 2) {
+      int *box = d.ent_box[mode];
+      box[0] = p.NY;
+      box[2] = p.NZ;
+      box[1] = box[3] = -1;
+    }
     struct E {
       int b, slot;
       int2 v;
@@ -2574,6 +3043,13 @@ static void build_lists(Plan &p, Dev &d) {
       const int64_t plane = (int64_t)p.NY * p.PX;
       const int k = (int)(idx / plane), j = (int)((idx % plane) / p.PX), i = (int)(idx % p.PX);
       if (i > p.nx || j > p.ny || k > p.nz) fail(FWD_ERR_INVALID_ARG, "entry outside the grid");
+      if (mode < 2) {
+        int *box = d.ent_box[mode];
+        box[0] = std::min(box[0], j);
+        box[1] = std::max(box[1], j);
+        box[2] = std::min(box[2], k);
+        box[3] = std::max(box[3], k);
+      }
       int bxi, byi, bzi, slot, sub;
       if (p.sched == 1) {
         if (k >= p.nz) return;   // no E update on the top plane: never used
@@ -2584,11 +3060,11 @@ static void build_lists(Plan &p, Dev &d) {
       } else {
         const int tx = i / t.vx;
         sub = i % t.vx;
-        bzi = k;
-        bxi = tx / p.bx;
-        slot = (j % p.by) * p.bx + (tx % p.bx);
+        bzi = k / t.bz;
+        bxi = tx / t.bx;
+        slot = ((k % t.bz) * t.by + j % t.by) * t.bx + (tx % t.bx);
       }
-      byi = j / p.by;
+      byi = j / t.by;
       const int b = p.order ? (byi * t.nbx + bxi) * t.nbz + bzi : (bzi * t.nby + byi) * t.nbx + bxi;
       ents.push_back({b, slot, make_int2(c | (kind << 2) | (sub << 3) | (s << 9), ref)});
     };
@@ -2598,7 +3074,7 @@ static void build_lists(Plan &p, Dev &d) {
     } else if (mode == 3) {
       // forward magnetic sources M'^n, added by the H update; the fused
       // schedule uses k_hsrc instead
-      if (p.sched != 1)
+      if (own_h)
         for (size_t q = 0; q < p.src_tg.size(); ++q)
           if (p.src_tg[q].c >= 3)
             place(p.src_tg[q].c - 3, 0, p.src_tg[q].s, p.src_tg[q].idx, (int)q);
@@ -2606,7 +3082,7 @@ static void build_lists(Plan &p, Dev &d) {
       for (int s = 0; s < p.ns; ++s)
         for (int node = 0; node < nn; ++node)
           if (p.rn_c[node] < 3) place(p.rn_c[node], 0, s, p.rn_idx[node], (s * nn + node) * 2 * nf);
-    } else if (p.sched != 1) {
+    } else if (own_h) {
       // magnetic adjoint sources M'^n, added by the H update (component c of
       // H = rn_c - 3); the fused schedule uses k_hinj instead
       for (int s = 0; s < p.ns; ++s)
@@ -2838,6 +3314,73 @@ static void launch_step(const StepArgs<T> &A, bool hist, dim3 grid, dim3 block, 
   else go(k_step<T, false>, grid, block, lds, st, kt, A);
 }
 
+// n: the step (the host's count); past the run's last step nothing is
+// injected, recorded or kept
+template <typename T>
+static void launch_leap(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool adj, int n,
+                        hipStream_t st, const KTime *kt) {
+  LeapArgs<T> L{};
+  L.fi = A.fields + ((n & 1) ? A.fbuf : 0);
+  L.fo = A.fields + ((n & 1) ? 0 : A.fbuf);
+  L.pi = A.psi + ((n & 1) ? A.pbuf : 0);
+  L.po = A.psi + ((n & 1) ? 0 : A.pbuf);
+  L.pe = A.psi;
+  L.ce = A.ce;
+  L.axt = A.axt;
+  L.axr = static_cast<const AxRow<T> *>(d.axr);
+  L.step = A.step;
+  L.step_w = A.step_w;
+  L.F6 = A.F6;
+  L.psi_src = A.psi_src;
+  L.hist_src = A.hist_src;
+  const size_t sz = sizeof(T);
+  L.PXb = (uint32_t)(A.PX * sz);
+  L.PLb = (uint32_t)(A.plane * sz);
+  L.Fb = (uint32_t)(A.F * sz);
+  L.LAb = (uint32_t)(A.LA * sz);
+  L.sXb = (uint32_t)(A.sX * sz);
+  L.sYb = (uint32_t)(A.sY * sz);
+  L.sZb = (uint32_t)(A.sZ * sz);
+  L.oYb = (uint32_t)(A.oY * sz);
+  L.oZb = (uint32_t)(A.oZ * sz);
+  L.nx = A.nx;
+  L.ny = A.ny;
+  L.nz = A.nz;
+  L.npml = A.npml;
+  L.LA = A.LA;
+  L.NY = A.NY;
+  L.dtmu = A.dtmu;
+  L.lean = A.lean;
+  L.nbx = A.nbx;
+  L.nby = A.nby;
+  L.nbz = A.nbz;
+  L.nblocks = A.nblocks;
+  L.xcd = A.xcd ? XCD_RUNS : 0;
+  L.order = A.order;
+  L.ns = A.ns;
+  L.dns = A.dns;
+  L.dnbx = A.dnbx;
+  L.dnby = A.dnby;
+  L.dnbz = A.dnbz;
+  L.tile_tab = A.tile_tab;
+  const int *box = d.ent_box[adj ? 1 : 0];
+  L.ej0 = box[0];
+  L.ej1 = n < p.nt ? box[1] : -1;
+  L.ek0 = box[2];
+  L.ek1 = box[3];
+  const int D = adj ? 1 : p.dec, m = n + 1, r = m / D & (p.kb - 1);
+  const bool hist = vol && n < p.nt && m % D == 0 && r != 0;
+  if (hist) L.hist = A.hist + (int64_t)(r - 1) * 3 * A.F;
+  const dim3 grid(A.nblocks), block(64);
+  if (A.nts) {
+    if (hist) go(k_leap<T, true, true>, grid, block, 0, st, kt, L, A);
+    else go(k_leap<T, false, true>, grid, block, 0, st, kt, L, A);
+  } else {
+    if (hist) go(k_leap<T, true, false>, grid, block, 0, st, kt, L, A);
+    else go(k_leap<T, false, false>, grid, block, 0, st, kt, L, A);
+  }
+}
+
 template <typename T>
 static void launch_h(const StepArgs<T> &A, int vx, dim3 grid, dim3 block, hipStream_t st,
                      const KTime *kt = nullptr, bool o4 = false, bool inj = false) {
@@ -2862,10 +3405,10 @@ static void launch_h(const StepArgs<T> &A, int vx, dim3 grid, dim3 block, hipStr
 #undef FWD_H
 }
 
-// enqueue step n (H update, E update; or the fused step), followed by the
+// enqueue step n (one launch; H update, E update; or the fused step), followed by the
 // block transform when sample n+1 closes a transform block.  If ev !=
-// nullptr, ev[0..1] time the H kernel, ev[2..3] the E kernel (fused: the one
-// kernel in ev[2..3], ev[0..1] recorded back to back) and ev[4..5] the block
+// nullptr, ev[0..1] time the H kernel, ev[2..3] the E kernel (one launch or
+// fused: the one kernel in ev[2..3], ev[0..1] recorded back to back) and ev[4..5] the block
 // transform (recorded back to back when there is none); *closed says which.
 template <typename T>
 static void enqueue_step(Plan &p, Dev &d, const WS &w, void *vol, bool adj, hipStream_t st,
@@ -2874,17 +3417,25 @@ static void enqueue_step(Plan &p, Dev &d, const WS &w, void *vol, bool adj, hipS
   const dim3 block(p.bx, p.by), grid(A.nblocks);
   const KTime th_ev = ev ? KTime{ev[0], ev[1]} : KTime{}, te_ev = ev ? KTime{ev[2], ev[3]} : KTime{};
   const KTime *kh = ev ? &th_ev : nullptr, *ke = ev ? &te_ev : nullptr;
-  // magnetic receiver nodes: adjoint sources before the H update; under the
-  // fused schedule the H transform after the step (the E update does not
-  // touch H)
+  const bool one = one_launch(p), hpre = one || p.sched == 1;
+  // magnetic nodes of the one-launch and fused steps: their sources go into H
+  // before the launch (every wave that recomputes a node then reads it); the
+  // fused step's H transform follows it (the E update does not touch H)
   const dim3 hgrid((p.ns * d.nh + 63) / 64), hblock(64);
-  if (d.nh > 0 && adj && p.sched == 1)
+  if (d.nh > 0 && adj && hpre)
     hipLaunchKernelGGL((k_hinj<T>), hgrid, hblock, 0, st, A, d.hn, d.nh, d.rn_c, d.rn_idx,
                        p.dt / kMu0);
-  if (!adj && p.src_kind == 1 && p.sched == 1)
+  if (!adj && p.src_kind == 1 && hpre)
     hipLaunchKernelGGL((k_hsrc<T>), dim3((d.ntg + 63) / 64), dim3(64), 0, st, A, d.src_s, d.src_c,
                        d.src_idx, d.ntg, p.dt / kMu0);
-  if (p.sched == 1) {
+  if (one) {
+    if (ev) {
+      (void)hipEventRecord(ev[0], st);
+      (void)hipEventRecord(ev[1], st);
+    }
+    const Tiling t = tiling(p);
+    launch_leap<T>(p, d, A, vol != nullptr, adj, n, st, ke);
+  } else if (p.sched == 1) {
     if (ev) {
       (void)hipEventRecord(ev[0], st);
       (void)hipEventRecord(ev[1], st);
@@ -3094,12 +3645,12 @@ static void run_steps_t(Plan &p, Dev &d, const WS &w, void *vol, bool adj, int n
     }
     HIP_CHECK(hipGetLastError());
   };
-  if (K < 2 || nsteps < K) {
+  if (K < 2 || nsteps < K || p.host_step + K > p.nt) {
     for (int t = 0; t < nsteps; ++t) eager(1, sample > 0 && t % sample == 0);
     return;
   }
   // graph of K steps, captured on a private stream and replayed on st
-  const int phase = p.host_step % (p.kb * D);
+  const int phase = p.host_step % (p.kb * D) * 2 + (p.host_step & 1);
   char key[256];
   snprintf(key, sizeof key, "%p/%p/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%llu/%llu", w.fields,
            vol, (int)adj, K, phase, p.bx, p.by, p.xcd, p.kb * 64 + D, p.vx, p.vxh, p.sched, p.kz, p.order,
@@ -3130,7 +3681,8 @@ static void run_steps_t(Plan &p, Dev &d, const WS &w, void *vol, bool adj, int n
   // replay the graph
   const int every = sample > 0 ? std::max(1, sample / K) : 0;
   int done = 0, chunk = 0;
-  while (nsteps - done >= K) {
+  // a replay holds no step past the run's last one (those take other launches)
+  while (nsteps - done >= K && p.host_step + K <= std::max(p.nt, 0)) {
     if (every && chunk % every == 0) {
       eager(K, true);
     } else {
@@ -3643,8 +4195,8 @@ void dev_adjoint_td(Plan &p, void *ws, size_t ws_bytes, void *scratch, size_t sc
 
 // ---------------------------------------------------------------------------
 // autotuner: time candidate schedules and tilings on the real buffers.  A
-// staged search (coordinate descent) instead of the full product: block
-// shape; vector widths; tile order x XCD remap; the fused schedule's shapes
+// staged search (coordinate descent) instead of the full product: the
+// one-launch step, or where it does not apply block shape and vector widths; tile order x XCD remap; the fused schedule's shapes
 // and planes per block; the transform block K (8 or 16, when the workspace
 // holds the longer history).  Each candidate first runs `steps` steps
 // untimed (its HIP graph is captured and instantiated there), then the same
@@ -3749,10 +4301,16 @@ double dev_autotune(Plan &p, void *ws, size_t ws_bytes, void *vol, size_t vol_by
       best = c;
     }
   };
-  // stage 1: block shapes (two-kernel schedule, one node per thread)
+  // stage 1: the one-launch step, which has no shape to choose (its two-kernel
+  // vector forms were slower wherever it applies); otherwise block shapes of
+  // the two kernels, one node per thread
   const int shapes[][2] = {{64, 4}, {64, 2}, {64, 1}, {32, 8}, {32, 4}, {16, 16},
                            {16, 8}, {16, 4}, {128, 2}, {256, 1}};
-  {
+  apply_cand(p, best);
+  const bool leap = one_launch(p);
+  if (leap) {
+    consider(TuneCand(best));
+  } else {
     const TuneCand base = best;
     for (auto &sh : shapes) {
       TuneCand c = base;
@@ -3762,7 +4320,7 @@ double dev_autotune(Plan &p, void *ws, size_t ws_bytes, void *vol, size_t vol_by
     }
   }
   // stage 2: 16-byte vectors (H only, then both)
-  if (!o4) {
+  if (!o4 && !leap) {
     const TuneCand base = best;
     for (int v : {1, 2}) {
       TuneCand c = base;

@@ -102,6 +102,7 @@ struct Plan {
   // adjoint targets = receiver nodes; CSR node -> (row r*ncomp+ci, w / dual volume)
   std::vector<int> at_ptr, at_row;
   std::vector<double> at_w;
+  bool h_on_walls = false;               // a magnetic source or receiver node lies on a high wall
 
   // ---- basis functions ----
   bool have_basis = false;

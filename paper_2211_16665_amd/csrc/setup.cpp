@@ -568,6 +568,17 @@ void set_model(Plan &p, const double *rho, const double *rho_v) {
     p.at_ptr.push_back((int)p.at_row.size());
   }
 
+  // H nodes of the high walls (i = nx, j = ny or k = nz) stay zero -- they
+  // difference E edges on the walls, which are never updated -- unless a
+  // magnetic source or the adjoint of a magnetic receiver touches one
+  p.h_on_walls = false;
+  auto on_wall = [&](int c, int64_t idx) {
+    const int64_t pl = p.plane();
+    return c >= 3 && (idx / pl == nz || idx % pl / p.PX == ny || idx % p.PX == nx);
+  };
+  for (const Target &tg : p.src_tg) p.h_on_walls |= on_wall(tg.c, tg.idx);
+  for (size_t q = 0; q < p.rn_c.size(); ++q) p.h_on_walls |= on_wall(p.rn_c[q], p.rn_idx[q]);
+
   if (p.dt != old_dt || p.nt != old_nt) {
     p.have_basis = false;
     p.basis.clear();
