@@ -320,6 +320,21 @@ static double dual_volume(const Plan &p, int c, int k, int j, int i) {
   }
 }
 
+// H nodes of the high walls (i = nx, j = ny or k = nz) stay zero -- they
+// difference E edges on the walls, which are never updated -- unless a
+// magnetic source or the adjoint of a magnetic receiver touches one.
+static bool h_on_high_walls(const Plan &p) {
+  auto on_wall = [&p](int c, int64_t idx) {
+    const int64_t pl = p.plane();
+    return c >= 3 && (idx / pl == p.nz || idx % pl / p.PX == p.ny || idx % p.PX == p.nx);
+  };
+  for (const Target &tg : p.src_tg)
+    if (on_wall(tg.c, tg.idx)) return true;
+  for (size_t q = 0; q < p.rn_c.size(); ++q)
+    if (on_wall(p.rn_c[q], p.rn_idx[q])) return true;
+  return false;
+}
+
 void set_model(Plan &p, const double *rho, const double *rho_v) {
   if (!rho) fail(FWD_ERR_INVALID_ARG, "rho is NULL");
   const int nx = p.nx, ny = p.ny, nz = p.nz;
@@ -568,17 +583,7 @@ void set_model(Plan &p, const double *rho, const double *rho_v) {
     p.at_ptr.push_back((int)p.at_row.size());
   }
 
-  // H nodes of the high walls (i = nx, j = ny or k = nz) stay zero -- they
-  // difference E edges on the walls, which are never updated -- unless a
-  // magnetic source or the adjoint of a magnetic receiver touches one
-  p.h_on_walls = false;
-  auto on_wall = [&](int c, int64_t idx) {
-    const int64_t pl = p.plane();
-    return c >= 3 && (idx / pl == nz || idx % pl / p.PX == ny || idx % p.PX == nx);
-  };
-  for (const Target &tg : p.src_tg) p.h_on_walls |= on_wall(tg.c, tg.idx);
-  for (size_t q = 0; q < p.rn_c.size(); ++q) p.h_on_walls |= on_wall(p.rn_c[q], p.rn_idx[q]);
-
+  p.h_on_walls = h_on_high_walls(p);
   if (p.dt != old_dt || p.nt != old_nt) {
     p.have_basis = false;
     p.basis.clear();
