@@ -1500,6 +1500,354 @@ __global__ void __launch_bounds__(256) k_update_e4(StepArgs<T> A) {
   }
 }
 
+// The same two updates as rows of waves (schedule 0 with 32-bit byte offsets
+// and no magnetic node on a high wall, as k_leap): one wave a block, 64 nodes
+// of one row, so that j and k, their coefficients, layer tests, images and
+// the byte offsets of the 21 rows that the differences read are scalar, each
+// load one scalar addition and one instruction.  The general kernels above
+// spend most of their time issuing per-lane index arithmetic and branches.
+// XL: nodes of the wave may lie in an x layer or within two nodes of an x
+// wall; YZ: the row may lie so in y or z; ENT: it may hold entries.
+// Rows of the high walls are not computed: H there stays zero.
+// Measured (one MI355X, 101x101x61 FP32), general -> rows: H update 14.6 ->
+// 9.6 us, E update 21.0 -> 14.0 us (12.6 without the history sample; its 37 MB
+// take 5 us at the rate of a large copy).
+template <typename T>
+__device__ __forceinline__ T d4(T a, T b, T c, T d) {
+  return fma(T(-1.0 / 24.0), d - a, T(9.0 / 8.0) * (c - b));
+}
+
+template <typename T, bool XL, bool YZ, bool ENT>
+__device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int i0,
+                                        int j, int k) {
+  const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];   // scalar loads: before the marker
+  asm volatile("; h4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));            // see leap_wave
+  const int tid = threadIdx.x, i = i0 + tid;
+  const int npml = L.npml, W = 2 * npml;
+  const uint32_t sz = sizeof(T);
+  const uint32_t x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
+  // rows j - 1, j + 2 and k - 1, k + 2: beyond a wall the image, negated
+  int ja = j - 1, jd = j + 2, ka = k - 1, kd = k + 2;
+  T gja = T(1), gjd = T(1), gka = T(1), gkd = T(1);
+  if constexpr (YZ) {
+    if (ja < 0) { ja = 1; gja = T(-1); }
+    if (jd > L.ny) { jd = L.ny - 1; gjd = T(-1); }
+    if (ka < 0) { ka = 1; gka = T(-1); }
+    if (kd > L.nz) { kd = L.nz - 1; gkd = T(-1); }
+  }
+  const uint32_t r = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb;      // row, x = 0
+  const uint32_t q = r + x0;
+  const uint32_t qja = (uint32_t)k * L.PLb + (uint32_t)ja * L.PXb + x0, qjc = q + L.PXb,
+                 qjd = (uint32_t)k * L.PLb + (uint32_t)jd * L.PXb + x0;
+  const uint32_t qka = (uint32_t)ka * L.PLb + (uint32_t)j * L.PXb + x0, qkc = q + L.PLb,
+                 qkd = (uint32_t)kd * L.PLb + (uint32_t)j * L.PXb + x0;
+  const __amdgpu_buffer_rsrc_t rI = rsrc_of(L.fi + (int64_t)s * L.F6), rX = rsrc_of(L.axt);
+  const T ex = bload<T>(rI, o, q), ey = bload<T>(rI, o, q + Fb), ez = bload<T>(rI, o, q + 2 * Fb);
+  T ex_ja = bload<T>(rI, o, qja), ez_ja = bload<T>(rI, o, qja + 2 * Fb);
+  const T ex_jc = bload<T>(rI, o, qjc), ez_jc = bload<T>(rI, o, qjc + 2 * Fb);
+  T ex_jd = bload<T>(rI, o, qjd), ez_jd = bload<T>(rI, o, qjd + 2 * Fb);
+  T ex_ka = bload<T>(rI, o, qka), ey_ka = bload<T>(rI, o, qka + Fb);
+  const T ex_kc = bload<T>(rI, o, qkc), ey_kc = bload<T>(rI, o, qkc + Fb);
+  T ex_kd = bload<T>(rI, o, qkd), ey_kd = bload<T>(rI, o, qkd + Fb);
+  T ey_ia, ez_ia, ey_id, ez_id;
+  const T ey_ic = bload<T>(rI, o, q + Fb + sz), ez_ic = bload<T>(rI, o, q + 2 * Fb + sz);
+  bool la = false, ld = false;
+  if constexpr (XL) {
+    la = i == 0;
+    ld = i == L.nx - 1;
+    const uint32_t oa = (uint32_t)(la ? 1 : i - 1) * sz, od = (uint32_t)(ld ? i : i + 2) * sz;
+    ey_ia = bload<T>(rI, oa, r + Fb);
+    ez_ia = bload<T>(rI, oa, r + 2 * Fb);
+    ey_id = bload<T>(rI, od, r + Fb);
+    ez_id = bload<T>(rI, od, r + 2 * Fb);
+  } else {
+    ey_ia = bload<T>(rI, o, q + Fb - sz);
+    ez_ia = bload<T>(rI, o, q + 2 * Fb - sz);
+    ey_id = bload<T>(rI, o, q + Fb + 2 * sz);
+    ez_id = bload<T>(rI, o, q + 2 * Fb + 2 * sz);
+  }
+  T hx = bload<T>(rI, o, q + 3 * Fb), hy = bload<T>(rI, o, q + 4 * Fb), hz = bload<T>(rI, o, q + 5 * Fb);
+  const T ih = bload<T>(rX, o, x0 + AX_IH * L.LAb);
+  // ---- layers: slab indices and memory ----
+  bool px = false, py = false, pz = false;
+  int lyh = 0, lzh = 0;
+  uint32_t cxh = 0;
+  if constexpr (YZ) {
+    py = pml_half(j, L.ny, npml, lyh);
+    pz = pml_half(k, L.nz, npml, lzh);
+  }
+  if constexpr (XL) {
+    px = (i < npml) | (i >= L.nx - npml);
+    cxh = (uint32_t)(i < npml ? i : i - L.nx + W) * sz;
+  }
+  T hx_y = T(0), hx_z = T(0), hy_z = T(0), hy_x = T(0), hz_x = T(0), hz_y = T(0);
+  Stretch<T> xh{};
+  const int64_t sp = (int64_t)s * L.psi_src;
+  const uint32_t r0 = (uint32_t)(k * L.NY + j) * (uint32_t)W * sz;
+  const uint32_t rYh = L.oYb + x0 + (uint32_t)(k * W + lyh) * L.PXb;
+  const uint32_t rZh = L.oZb + x0 + (uint32_t)(lzh * L.NY + j) * L.PXb;
+  if constexpr (XL || YZ) {
+    const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.pi + sp);
+    if (YZ && py) {
+      hx_y = bload<T>(rP, o, rYh);
+      hz_y = bload<T>(rP, o, rYh + L.sYb);
+    }
+    if (YZ && pz) {
+      hx_z = bload<T>(rP, o, rZh);
+      hy_z = bload<T>(rP, o, rZh + L.sZb);
+    }
+    if (XL && px) {
+      hy_x = bload<T>(rP, cxh, r0);
+      hz_x = bload<T>(rP, cxh, r0 + L.sXb);
+      xh = {bload<T>(rX, o, x0 + AX_BH * L.LAb), bload<T>(rX, o, x0 + AX_AH * L.LAb),
+            bload<T>(rX, o, x0 + AX_KH * L.LAb)};
+    }
+  }
+  if constexpr (ENT) {
+    const int n = L.step[0] + 1;
+    int lo, hi;
+    entry_slice_at(A, b, n, tid, lo, hi);
+    if (lo < hi) {
+      Vec<T, 1> vx = vec1(hx), vy = vec1(hy), vz = vec1(hz);
+      inject_h<T, 1>(A, lo, hi, s, n, vx, vy, vz);
+      hx = vx.v[0];
+      hy = vy.v[0];
+      hz = vz.v[0];
+    }
+  }
+  if constexpr (YZ) {
+    ex_ja *= gja; ez_ja *= gja; ex_jd *= gjd; ez_jd *= gjd;
+    ex_ka *= gka; ey_ka *= gka; ex_kd *= gkd; ey_kd *= gkd;
+  }
+  if constexpr (XL) {
+    ey_ia = la ? -ey_ia : ey_ia;
+    ez_ia = la ? -ez_ia : ez_ia;
+    ey_id = ld ? -ey_id : ey_id;
+    ez_id = ld ? -ez_id : ez_id;
+  }
+  const T mc = -L.dtmu, zero = T(0);
+  const Stretch<T> yh{yj.bh, yj.ah, yj.kh}, zh{zk.bh, zk.ah, zk.kh};
+  const T Hx = curl_update<YZ, YZ>(hx, mc, d4(ez_ja, ez, ez_jc, ez_jd), zero, yj.ih, py, hx_y, yh,
+                                   d4(ey_ka, ey, ey_kc, ey_kd), zero, zk.ih, pz, hx_z, zh);
+  const T Hy = curl_update<YZ, XL>(hy, mc, d4(ex_ka, ex, ex_kc, ex_kd), zero, zk.ih, pz, hy_z, zh,
+                                   d4(ez_ia, ez, ez_ic, ez_id), zero, ih, px, hy_x, xh);
+  const T Hz = curl_update<XL, YZ>(hz, mc, d4(ey_ia, ey, ey_ic, ey_id), zero, ih, px, hz_x, xh,
+                                   d4(ex_ja, ex, ex_jc, ex_jd), zero, yj.ih, py, hz_y, yh);
+  const __amdgpu_buffer_rsrc_t rO = rsrc_of(L.fo + (int64_t)s * L.F6);
+  bstore<false>(Hx, rO, o, q + 3 * Fb);
+  bstore<false>(Hy, rO, o, q + 4 * Fb);
+  bstore<false>(Hz, rO, o, q + 5 * Fb);
+  if constexpr (XL || YZ) {
+    const __amdgpu_buffer_rsrc_t rQ = rsrc_of(L.po + sp);
+    if (YZ && py) {
+      bstore<false>(hx_y, rQ, o, rYh);
+      bstore<false>(hz_y, rQ, o, rYh + L.sYb);
+    }
+    if (YZ && pz) {
+      bstore<false>(hx_z, rQ, o, rZh);
+      bstore<false>(hy_z, rQ, o, rZh + L.sZb);
+    }
+    if (XL && px) {
+      bstore<false>(hy_x, rQ, cxh, r0);
+      bstore<false>(hz_x, rQ, cxh, r0 + L.sXb);
+    }
+  }
+}
+
+template <typename T, bool HIST, bool XL, bool YZ, bool ENT>
+__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int i0,
+                                        int j, int k) {
+  const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];
+  asm volatile("; e4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));
+  const int tid = threadIdx.x, i = i0 + tid;
+  const int npml = L.npml, W = 2 * npml;
+  const uint32_t sz = sizeof(T);
+  const uint32_t x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
+  // rows j - 2, j - 1, j + 1 and k - 2, k - 1, k + 1: beyond a wall the image
+  // (index -1 is 0, index n is n - 1); differences of the rows on a low wall
+  // reach no stored result
+  int ja = j - 2, jb = j - 1, jd = j + 1, ka = k - 2, kb = k - 1, kd = k + 1;
+  if constexpr (YZ) {
+    ja = max(ja, 0);
+    jb = max(jb, 0);
+    jd = min(jd, L.ny - 1);
+    ka = max(ka, 0);
+    kb = max(kb, 0);
+    kd = min(kd, L.nz - 1);
+  }
+  const uint32_t rk = (uint32_t)k * L.PLb, rj = (uint32_t)j * L.PXb;
+  const uint32_t r = rk + rj, q = r + x0;
+  const uint32_t qja = rk + (uint32_t)ja * L.PXb + x0, qjb = rk + (uint32_t)jb * L.PXb + x0,
+                 qjd = rk + (uint32_t)jd * L.PXb + x0;
+  const uint32_t qka = (uint32_t)ka * L.PLb + rj + x0, qkb = (uint32_t)kb * L.PLb + rj + x0,
+                 qkd = (uint32_t)kd * L.PLb + rj + x0;
+  const int64_t so = (int64_t)s * L.F6;
+  const __amdgpu_buffer_rsrc_t rI = rsrc_of(L.fi + so), rO = rsrc_of(L.fo + so), rC = rsrc_of(L.ce),
+                               rX = rsrc_of(L.axt);
+  const uint32_t fx = 3 * Fb, fy = 4 * Fb, fz = 5 * Fb;
+  const T hx = bload<T>(rO, o, q + fx), hy = bload<T>(rO, o, q + fy), hz = bload<T>(rO, o, q + fz);
+  const T hx_ja = bload<T>(rO, o, qja + fx), hz_ja = bload<T>(rO, o, qja + fz);
+  const T hx_jb = bload<T>(rO, o, qjb + fx), hz_jb = bload<T>(rO, o, qjb + fz);
+  const T hx_jd = bload<T>(rO, o, qjd + fx), hz_jd = bload<T>(rO, o, qjd + fz);
+  const T hx_ka = bload<T>(rO, o, qka + fx), hy_ka = bload<T>(rO, o, qka + fy);
+  const T hx_kb = bload<T>(rO, o, qkb + fx), hy_kb = bload<T>(rO, o, qkb + fy);
+  const T hx_kd = bload<T>(rO, o, qkd + fx), hy_kd = bload<T>(rO, o, qkd + fy);
+  T hy_ia, hz_ia, hy_ib, hz_ib, hy_id, hz_id;
+  if constexpr (XL) {
+    const uint32_t oa = (uint32_t)max(i - 2, 0) * sz, ob = (uint32_t)max(i - 1, 0) * sz,
+                   od = (uint32_t)min(i + 1, L.nx - 1) * sz;
+    hy_ia = bload<T>(rO, oa, r + fy);
+    hz_ia = bload<T>(rO, oa, r + fz);
+    hy_ib = bload<T>(rO, ob, r + fy);
+    hz_ib = bload<T>(rO, ob, r + fz);
+    hy_id = bload<T>(rO, od, r + fy);
+    hz_id = bload<T>(rO, od, r + fz);
+  } else {
+    hy_ia = bload<T>(rO, o, q + fy - 2 * sz);
+    hz_ia = bload<T>(rO, o, q + fz - 2 * sz);
+    hy_ib = bload<T>(rO, o, q + fy - sz);
+    hz_ib = bload<T>(rO, o, q + fz - sz);
+    hy_id = bload<T>(rO, o, q + fy + sz);
+    hz_id = bload<T>(rO, o, q + fz + sz);
+  }
+  const T ex = bload<T>(rI, o, q), ey = bload<T>(rI, o, q + Fb), ez = bload<T>(rI, o, q + 2 * Fb);
+  const T cx = bload<T>(rC, o, q), cy = bload<T>(rC, o, q + Fb), cz = bload<T>(rC, o, q + 2 * Fb);
+  const T ihd = bload<T>(rX, o, x0 + AX_IHD * L.LAb);
+  // ---- layers ----
+  const bool j_lo = !YZ || j >= 1, k_lo = !YZ || k >= 1, i_lo = !XL || i >= 1;
+  bool pxn = false, pyn = false, pzn = false;
+  int lyn = 0, lzn = 0;
+  uint32_t cxn = 0;
+  if constexpr (YZ) {
+    pyn = j_lo && pml_int(j, L.ny, npml, lyn);
+    pzn = k_lo && pml_int(k, L.nz, npml, lzn);
+  }
+  if constexpr (XL) {
+    pxn = i_lo & ((i < npml) | (i > L.nx - npml));
+    cxn = (uint32_t)(i < npml ? i : i - L.nx + W - 1) * sz;
+  }
+  T ex_y = T(0), ex_z = T(0), ey_z = T(0), ey_x = T(0), ez_x = T(0), ez_y = T(0);
+  Stretch<T> xn{};
+  const __amdgpu_buffer_rsrc_t rE = rsrc_of(L.pe + (int64_t)s * L.psi_src);
+  const uint32_t r0 = (uint32_t)(k * L.NY + j) * (uint32_t)W * sz + 2 * L.sXb;
+  const uint32_t rYn = L.oYb + x0 + 2 * L.sYb + (uint32_t)(k * W + lyn) * L.PXb;
+  const uint32_t rZn = L.oZb + x0 + 2 * L.sZb + (uint32_t)(lzn * L.NY + j) * L.PXb;
+  if (YZ && pyn) {
+    ex_y = bload<T>(rE, o, rYn);
+    ez_y = bload<T>(rE, o, rYn + L.sYb);
+  }
+  if (YZ && pzn) {
+    ex_z = bload<T>(rE, o, rZn);
+    ey_z = bload<T>(rE, o, rZn + L.sZb);
+  }
+  if (XL && pxn) {
+    ey_x = bload<T>(rE, cxn, r0);
+    ez_x = bload<T>(rE, cxn, r0 + L.sXb);
+    xn = {bload<T>(rX, o, x0 + AX_BN * L.LAb), bload<T>(rX, o, x0 + AX_AN * L.LAb),
+          bload<T>(rX, o, x0 + AX_KN * L.LAb)};
+  }
+  int lo = 0, hi = 0, n = 0;
+  if constexpr (ENT) {
+    n = L.step[0] + 1;
+    entry_slice_at(A, b, n, tid, lo, hi);
+  }
+  const T zero = T(0);
+  const Stretch<T> yn{yj.bn, yj.an, yj.kn}, zn{zk.bn, zk.an, zk.kn};
+  T e1x = curl_update<YZ, YZ>(ex, cx, d4(hz_ja, hz_jb, hz, hz_jd), zero, yj.ihd, pyn, ex_y, yn,
+                              d4(hy_ka, hy_kb, hy, hy_kd), zero, zk.ihd, pzn, ex_z, zn);
+  T e1y = curl_update<YZ, XL>(ey, cy, d4(hx_ka, hx_kb, hx, hx_kd), zero, zk.ihd, pzn, ey_z, zn,
+                              d4(hz_ia, hz_ib, hz, hz_id), zero, ihd, pxn, ey_x, xn);
+  T e1z = curl_update<XL, YZ>(ez, cz, d4(hy_ia, hy_ib, hy, hy_id), zero, ihd, pxn, ez_x, xn,
+                              d4(hx_ja, hx_jb, hx, hx_jd), zero, yj.ihd, pyn, ez_y, yn);
+  if (ENT && lo < hi) {
+    double inj[3];
+    inject_all<T, 1>(A, lo, hi, s, n, inj);
+    e1x -= (T)((double)cx * inj[0]);
+    e1y -= (T)((double)cy * inj[1]);
+    e1z -= (T)((double)cz * inj[2]);
+  }
+  if constexpr (XL) {                    // edges on the low x wall keep their value (zero)
+    e1y = i_lo ? e1y : ey;
+    e1z = i_lo ? e1z : ez;
+  }
+  const bool row_x = j_lo && k_lo, row_y = k_lo, row_z = j_lo;
+  if (row_x) bstore<false>(e1x, rO, o, q);
+  if (row_y) bstore<false>(e1y, rO, o, q + Fb);
+  if (row_z) bstore<false>(e1z, rO, o, q + 2 * Fb);
+  if constexpr (HIST) {
+    const __amdgpu_buffer_rsrc_t rH = rsrc_of(L.hist + (int64_t)s * L.hist_src);
+    if (row_x) bstore<false>(e1x, rH, o, q);
+    if (row_y) bstore<false>(e1y, rH, o, q + Fb);
+    if (row_z) bstore<false>(e1z, rH, o, q + 2 * Fb);
+  }
+  if (YZ && pyn) {
+    if (row_x) bstore<false>(ex_y, rE, o, rYn);
+    if (row_z) bstore<false>(ez_y, rE, o, rYn + L.sYb);
+  }
+  if (YZ && pzn) {
+    if (row_x) bstore<false>(ex_z, rE, o, rZn);
+    if (row_y) bstore<false>(ey_z, rE, o, rZn + L.sZb);
+  }
+  if (XL && pxn) {
+    if (row_y) bstore<false>(ey_x, rE, cxn, r0);
+    if (row_z) bstore<false>(ez_x, rE, cxn, r0 + L.sXb);
+  }
+  if (ENT && lo < hi) {
+    const Vec<T, 1> e1[3] = {vec1(e1x), vec1(e1y), vec1(e1z)};
+    const unsigned ok[3] = {row_x ? 1u : 0u, i_lo && row_y ? 1u : 0u, i_lo && row_z ? 1u : 0u};
+    const Vec<T, 1> hh[3] = {vec1(hx), vec1(hy), vec1(hz)};
+    record_all<T, 1>(A, lo, hi, s, n, e1, ok, hh);
+  }
+}
+
+// Which variant a row takes: a layer or a wall (within the two nodes that the
+// differences reach) in x, and in y or z
+template <typename T>
+__device__ __forceinline__ void row_kind(const LeapArgs<T> &L, int i0, int j, int k, bool &xl, bool &yz) {
+  const int np = max(L.npml, 2);
+  xl = !L.lean || i0 < np || i0 + 64 > L.nx - np;
+  yz = !L.lean || j < np || j >= L.ny - np || k < np || k >= L.nz - np;
+}
+
+template <typename T, bool INJ>
+__global__ void __launch_bounds__(64) k_rows_h4(LeapArgs<T> L, StepArgs<T> A) {
+  int bx, j, k, s;
+  const int b = tile_of(L, bx, j, k, s);
+  const int i0 = bx * 64;
+  if (i0 + (int)threadIdx.x >= L.nx) return;
+  bool xl, yz;
+  row_kind(L, i0, j, k, xl, yz);
+  if (INJ && A.tile_tab[b] >= 0)
+    h4_wave<T, true, true, true>(L, A, s, b, i0, j, k);
+  else if (xl) {
+    if (yz) h4_wave<T, true, true, false>(L, A, s, b, i0, j, k);
+    else h4_wave<T, true, false, false>(L, A, s, b, i0, j, k);
+  } else {
+    if (yz) h4_wave<T, false, true, false>(L, A, s, b, i0, j, k);
+    else h4_wave<T, false, false, false>(L, A, s, b, i0, j, k);
+  }
+}
+
+template <typename T, bool HIST>
+__global__ void __launch_bounds__(64) k_rows_e4(LeapArgs<T> L, StepArgs<T> A) {
+  int bx, j, k, s;
+  const int b = tile_of(L, bx, j, k, s);
+  const int i0 = bx * 64;
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = L.step[0] + 1;
+  if (i0 + (int)threadIdx.x >= L.nx) return;
+  bool xl, yz;
+  row_kind(L, i0, j, k, xl, yz);
+  if (j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1)
+    e4_wave<T, HIST, true, true, true>(L, A, s, b, i0, j, k);
+  else if (xl) {
+    if (yz) e4_wave<T, HIST, true, true, false>(L, A, s, b, i0, j, k);
+    else e4_wave<T, HIST, true, false, false>(L, A, s, b, i0, j, k);
+  } else {
+    if (yz) e4_wave<T, HIST, false, true, false>(L, A, s, b, i0, j, k);
+    else e4_wave<T, HIST, false, false, false>(L, A, s, b, i0, j, k);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Fused step (one launch per leapfrog step).  A block of bx x by threads
 // owns the columns (i, j) = (x0 + tx, y0 + ty) of a tile and the planes
@@ -2947,7 +3295,7 @@ static WS carve(const Plan &p, void *ws) {
 // one step = one launch (k_leap), two launches (H, E) or one fused launch
 // ---------------------------------------------------------------------------
 // Tiling: (bx x by) threads over x-y; tile b = (bz * nby + by) * nbx + bx.
-// One launch: 64 x nodes of one row.  Two kernels: each thread a vector of VX
+// Rows of waves: 64 x nodes of one row.  Two kernels: each thread a vector of VX
 // x nodes, one plane per tile row (bz = k).  Fused: one x node per thread, kz planes per tile (bz = chunk).
 struct Tiling {
   int nbx, nby, nbz, nblocks, vx;
@@ -2955,20 +3303,23 @@ struct Tiling {
   size_t lds;   // dynamic LDS bytes per block (fused)
 };
 
-// The one-launch step k_leap carries out schedule 0 at order 2 with one node
-// per thread.  It is left to the two kernels where its 32-bit byte offsets
-// do not reach (a source's fields, CPML memory or history slot of 4 GB and
-// more) and where magnetic nodes lie on the high walls (it skips those rows).
-// The two kernels on one node per thread are slower on every grid measured
-// (FP32 us a step: 101x101x61 30.1 against 17.3, 200x200x100 with 4 sources
-// 546 against 381; FP64: 32x32x32 13.3 against 8.2, 128x128x96 113 against
-// 85); their 16-byte vector forms remain a choice of the caller.
-static bool one_launch(const Plan &p) {
+// Schedule 0 with one node per thread runs as rows of waves: the one-launch
+// step k_leap at order 2, k_rows_h4 and k_rows_e4 at order 4.  It is left to
+// the general kernels where 32-bit byte offsets do not reach (a source's
+// fields, CPML memory or history slot of 4 GB and more) and where magnetic
+// nodes lie on the high walls (the rows of those walls are skipped).
+// The two general kernels on one node per thread are slower on every grid
+// measured (order 2, FP32 us a step: 101x101x61 30.1 against 17.3,
+// 200x200x100 with 4 sources 546 against 381; FP64: 32x32x32 13.3 against
+// 8.2, 128x128x96 113 against 85; order 4, FP32, 101x101x61: 35.6 against
+// 23.6); at order 2 their 16-byte vector forms remain a choice of the caller.
+static bool wave_rows(const Plan &p) {
   const uint64_t lim = (uint64_t)1 << 32;
-  return p.sched == 0 && p.fd_order == 2 && p.vx == 1 && p.vxh == 1 && !p.h_on_walls &&
+  return p.sched == 0 && p.vx == 1 && p.vxh == 1 && !p.h_on_walls &&
          6 * (uint64_t)p.field_elems() * p.tsize() < lim &&
          (uint64_t)p.psi_elems_per_source() * p.tsize() < lim;
 }
+static bool one_launch(const Plan &p) { return p.fd_order == 2 && wave_rows(p); }
 
 static Tiling tiling(const Plan &p, bool h_update = false) {
   if (p.bx * p.by > 256) fail(FWD_ERR_INVALID_ARG, "block x * block y must be <= 256");
@@ -2976,7 +3327,7 @@ static Tiling tiling(const Plan &p, bool h_update = false) {
   t.bx = p.bx;
   t.by = p.by;
   t.bz = 1;
-  if (one_launch(p)) {
+  if (wave_rows(p)) {
     // one wave a block: 64 nodes of a row (the nodes of the high walls are
     // skipped, see k_leap)
     t.vx = 1;
@@ -3317,8 +3668,7 @@ static void launch_step(const StepArgs<T> &A, bool hist, dim3 grid, dim3 block, 
 // n: the step (the host's count); past the run's last step nothing is
 // injected, recorded or kept
 template <typename T>
-static void launch_leap(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool adj, int n,
-                        hipStream_t st, const KTime *kt) {
+static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool adj, int n) {
   LeapArgs<T> L{};
   L.fi = A.fields + ((n & 1) ? A.fbuf : 0);
   L.fo = A.fields + ((n & 1) ? 0 : A.fbuf);
@@ -3371,6 +3721,14 @@ static void launch_leap(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool ad
   const int D = adj ? 1 : p.dec, m = n + 1, r = m / D & (p.kb - 1);
   const bool hist = vol && n < p.nt && m % D == 0 && r != 0;
   if (hist) L.hist = A.hist + (int64_t)(r - 1) * 3 * A.F;
+  return L;
+}
+
+template <typename T>
+static void launch_leap(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool adj, int n,
+                        hipStream_t st, const KTime *kt) {
+  const LeapArgs<T> L = leap_args<T>(p, d, A, vol, adj, n);
+  const bool hist = L.hist != nullptr;
   const dim3 grid(A.nblocks), block(64);
   if (A.nts) {
     if (hist) go(k_leap<T, true, true>, grid, block, 0, st, kt, L, A);
@@ -3456,11 +3814,20 @@ static void enqueue_step(Plan &p, Dev &d, const WS &w, void *vol, bool adj, hipS
     Ah.tl_off = hinj ? d.tl_off[hm] : nullptr;
     Ah.tl_ent = hinj ? d.tl_ent[hm] : nullptr;
     const bool o4 = p.fd_order == 4;
-    launch_h<T>(Ah, p.vxh, dim3(Ah.nblocks), block, st, kh, o4, hinj);
-    // with a decimated volume transform only the steps whose sample enters
-    // it keep history
-    const int D = adj ? 1 : p.dec;
-    launch_e<T>(A, p.vx, vol != nullptr && (n + 1) % D == 0, grid, block, st, ke, o4);
+    if (o4 && wave_rows(p)) {
+      const LeapArgs<T> L = leap_args<T>(p, d, A, vol != nullptr, adj, n);
+      const dim3 row(64);
+      if (hinj && n < p.nt) go(k_rows_h4<T, true>, grid, row, 0, st, kh, L, Ah);
+      else go(k_rows_h4<T, false>, grid, row, 0, st, kh, L, Ah);
+      if (L.hist) go(k_rows_e4<T, true>, grid, row, 0, st, ke, L, A);
+      else go(k_rows_e4<T, false>, grid, row, 0, st, ke, L, A);
+    } else {
+      launch_h<T>(Ah, p.vxh, dim3(Ah.nblocks), block, st, kh, o4, hinj);
+      // with a decimated volume transform only the steps whose sample enters
+      // it keep history
+      const int D = adj ? 1 : p.dec;
+      launch_e<T>(A, p.vx, vol != nullptr && (n + 1) % D == 0, grid, block, st, ke, o4);
+    }
   }
   // the block transform after the step whose sample closes a block; it reads
   // the counter the E update has just written (step n)
@@ -4301,13 +4668,13 @@ double dev_autotune(Plan &p, void *ws, size_t ws_bytes, void *vol, size_t vol_by
       best = c;
     }
   };
-  // stage 1: the one-launch step, which has no shape to choose (its two-kernel
-  // vector forms were slower wherever it applies); otherwise block shapes of
-  // the two kernels, one node per thread
+  // stage 1: rows of waves, which have no shape to choose (at order 2 the two
+  // kernels' vector forms were slower wherever they apply); otherwise block
+  // shapes of the two kernels, one node per thread
   const int shapes[][2] = {{64, 4}, {64, 2}, {64, 1}, {32, 8}, {32, 4}, {16, 16},
                            {16, 8}, {16, 4}, {128, 2}, {256, 1}};
   apply_cand(p, best);
-  const bool leap = one_launch(p);
+  const bool leap = wave_rows(p);
   if (leap) {
     consider(TuneCand(best));
   } else {
