@@ -1805,8 +1805,8 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
 template <typename T>
 __device__ __forceinline__ void row_kind(const LeapArgs<T> &L, int i0, int j, int k, bool &xl, bool &yz) {
   const int np = max(L.npml, 2);
-  xl = !L.lean || i0 < np || i0 + 64 > L.nx - np;
-  yz = !L.lean || j < np || j >= L.ny - np || k < np || k >= L.nz - np;
+  xl = !L.lean || i0 <= np || i0 + 64 > L.nx - np;
+  yz = !L.lean || j <= np || j >= L.ny - np || k <= np || k >= L.nz - np;
 }
 
 template <typename T, bool INJ>
@@ -2657,6 +2657,409 @@ __global__ void __launch_bounds__(256) k_td_h(StepArgs<T> A, const T *Enew, cons
     if (okx) Ad.ex[q] += gather_e4<T>(ax(1, 1), k, A.nz) + gather_e4<T>(ax(2, 2), j, A.ny);
     if (oky) Ad.ey[q] += gather_e4<T>(ax(0, 2), k, A.nz) + gather_e4<T>(ax(2, 1), i, A.nx);
     if (okz) Ad.ez[q] += gather_e4<T>(ax(0, 1), j, A.ny) + gather_e4<T>(ax(1, 2), i, A.nx);
+  }
+}
+
+// The reverse step of order 2 as rows of waves (where k_leap runs the forward
+// steps): one wave a block, 64 nodes of one row; rows, coefficients, layer
+// tests and offsets are scalar, and the x neighbour's term comes from the lane
+// beside (the wave's edge lane computes it).  The entry lists of the adjoint
+// runs add the receivers' sensitivities to the owner's new multiplier, so the
+// two launches are the whole reverse step.  XL, YZ, ENT: as k_leap.
+// The same operations in the same order as the general kernels.
+// Multipliers and memory on the high walls stay zero: their rows are skipped.
+// Measured (one MI355X, 101x101x61 FP32), general -> rows: H multipliers 27.3
+// -> 11.8 us, E multipliers and product 35.4 -> 21.3 us (its 94 MB, a third of
+// them the FP64 sums, take 13 us at the rate of a cached copy), and the two
+// sensitivity launches of 4.8 us a step are gone.
+
+// aD / h of one derivative: ad its multiplier, p its memory's
+template <bool P, typename T>
+__device__ __forceinline__ T td_ad(T ad, T h, bool in, T p, T kinv, T a) {
+  T v = ad;
+  if constexpr (P) {
+    const T d = ad * kinv + a * (ad + p);
+    v = in ? d : v;
+  }
+  return v * h;
+}
+
+// -Re sum_k C_k z_k (k_td_sens) of the listed node, added to v
+template <typename T>
+__device__ __forceinline__ T td_sens_of(const StepArgs<T> &A, const double2 *C, const double2 *z, int s,
+                                        int node, T v) {
+  double g = 0.0;
+  for (int kf = 0; kf < A.nf; ++kf) {
+    const double2 c = C[((int64_t)s * A.nn + node) * A.nf + kf];
+    g -= c.x * z[kf].x - c.y * z[kf].y;
+  }
+  return v + (T)g;
+}
+
+template <typename T, bool XL, bool YZ, bool ENT>
+__device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int i0,
+                                          int j, int k, const double2 *C, const double2 *z) {
+  const AxRow<T> yj = L.axr[L.LA + j], yp = L.axr[L.LA + j + 1], zk = L.axr[2 * L.LA + k],
+                 zp = L.axr[2 * L.LA + k + 1], xr = L.axr[min(i0 + 64, L.nx)];
+  asm volatile("; tde %0" ::"n"(XL * 4 + YZ * 2 + ENT));   // see leap_wave
+  const int tid = threadIdx.x, i = i0 + tid;
+  const int npml = L.npml, W = 2 * npml;
+  const uint32_t sz = sizeof(T), x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
+  const uint32_t q = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0, qj = q + L.PXb, qk = q + L.PLb;
+  const __amdgpu_buffer_rsrc_t rA = rsrc_of(L.fi + (int64_t)s * L.F6), rO = rsrc_of(L.fo + (int64_t)s * L.F6),
+                               rC = rsrc_of(L.ce), rX = rsrc_of(L.axt);
+  const T ax = bload<T>(rA, o, q), ay = bload<T>(rA, o, q + Fb), az = bload<T>(rA, o, q + 2 * Fb);
+  const T ax_j = bload<T>(rA, o, qj), az_j = bload<T>(rA, o, qj + 2 * Fb);
+  const T ax_k = bload<T>(rA, o, qk), ay_k = bload<T>(rA, o, qk + Fb);
+  const T cx = bload<T>(rC, o, q), cy = bload<T>(rC, o, q + Fb), cz = bload<T>(rC, o, q + 2 * Fb);
+  const T cx_j = bload<T>(rC, o, qj), cz_j = bload<T>(rC, o, qj + 2 * Fb);
+  const T cx_k = bload<T>(rC, o, qk), cy_k = bload<T>(rC, o, qk + Fb);
+  const T hx = bload<T>(rA, o, q + 3 * Fb), hy = bload<T>(rA, o, q + 4 * Fb), hz = bload<T>(rA, o, q + 5 * Fb);
+  const T ihd = bload<T>(rX, o, x0 + AX_IHD * L.LAb);
+  // the edge lane's neighbour at i0 + 64 (edges on the high wall contribute nothing)
+  const bool right = i0 + 64 < L.nx;
+  T ay_r = T(0), az_r = T(0), cy_r = T(0), cz_r = T(0);
+  if (right && tid == 63) {
+    ay_r = bload<T>(rA, o, q + Fb + sz);
+    az_r = bload<T>(rA, o, q + 2 * Fb + sz);
+    cy_r = bload<T>(rC, o, q + Fb + sz);
+    cz_r = bload<T>(rC, o, q + 2 * Fb + sz);
+  }
+  // ---- layers ----
+  bool py = false, pz = false, px = false;                  // half nodes: memory of H
+  bool nyj = false, nyp = false, nzk = false, nzp = false;  // nodes j, j + 1, k, k + 1: memory of E
+  bool nx0 = false, nxr = false;                            // nodes i and, of the edge lane, i0 + 64
+  int ly = 0, lz = 0, lyj = 0, lyp = 0, lzk = 0, lzp = 0, lxr = 0;
+  uint32_t cxh = 0, cxn = 0;
+  if constexpr (YZ) {
+    py = pml_half(j, L.ny, npml, ly);
+    pz = pml_half(k, L.nz, npml, lz);
+    nyj = j >= 1 && pml_int(j, L.ny, npml, lyj);
+    nyp = j + 1 < L.ny && pml_int(j + 1, L.ny, npml, lyp);
+    nzk = k >= 1 && pml_int(k, L.nz, npml, lzk);
+    nzp = k + 1 < L.nz && pml_int(k + 1, L.nz, npml, lzp);
+  }
+  if constexpr (XL) {
+    px = (i < npml) | (i >= L.nx - npml);
+    nx0 = (i >= 1) & ((i < npml) | (i > L.nx - npml));
+    cxh = (uint32_t)(i < npml ? i : i - L.nx + W) * sz;
+    cxn = (uint32_t)(i < npml ? i : i - L.nx + W - 1) * sz;
+    nxr = right && pml_int(i0 + 64, L.nx, npml, lxr);
+  }
+  const int64_t sp = (int64_t)s * L.psi_src;
+  const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.pe + sp);
+  const uint32_t r0 = (uint32_t)(k * L.NY + j) * (uint32_t)W * sz;
+  const uint32_t oY = L.oYb + x0, oZ = L.oZb + x0;
+  auto rowY = [&](int l) { return oY + (uint32_t)(k * W + l) * L.PXb; };
+  auto rowZ = [&](int l) { return oZ + (uint32_t)(l * L.NY + j) * L.PXb; };
+  T p_hx_y = T(0), p_hz_y = T(0), p_hx_z = T(0), p_hy_z = T(0), p_hy_x = T(0), p_hz_x = T(0);
+  T ex_yj = T(0), ez_yj = T(0), ex_yp = T(0), ez_yp = T(0), ex_zk = T(0), ey_zk = T(0), ex_zp = T(0),
+    ey_zp = T(0), ey_x = T(0), ez_x = T(0), ey_xr = T(0), ez_xr = T(0);
+  T bh = T(0), kn = T(0), an = T(0);
+  if constexpr (YZ) {
+    if (py) {
+      p_hx_y = bload<T>(rP, o, rowY(ly));
+      p_hz_y = bload<T>(rP, o, rowY(ly) + L.sYb);
+    }
+    if (pz) {
+      p_hx_z = bload<T>(rP, o, rowZ(lz));
+      p_hy_z = bload<T>(rP, o, rowZ(lz) + L.sZb);
+    }
+    if (nyj) {
+      ex_yj = bload<T>(rP, o, rowY(lyj) + 2 * L.sYb);
+      ez_yj = bload<T>(rP, o, rowY(lyj) + 3 * L.sYb);
+    }
+    if (nyp) {
+      ex_yp = bload<T>(rP, o, rowY(lyp) + 2 * L.sYb);
+      ez_yp = bload<T>(rP, o, rowY(lyp) + 3 * L.sYb);
+    }
+    if (nzk) {
+      ex_zk = bload<T>(rP, o, rowZ(lzk) + 2 * L.sZb);
+      ey_zk = bload<T>(rP, o, rowZ(lzk) + 3 * L.sZb);
+    }
+    if (nzp) {
+      ex_zp = bload<T>(rP, o, rowZ(lzp) + 2 * L.sZb);
+      ey_zp = bload<T>(rP, o, rowZ(lzp) + 3 * L.sZb);
+    }
+  }
+  if constexpr (XL) {
+    if (px) {
+      p_hy_x = bload<T>(rP, cxh, r0);
+      p_hz_x = bload<T>(rP, cxh, r0 + L.sXb);
+      bh = bload<T>(rX, o, x0 + AX_BH * L.LAb);
+    }
+    if (nx0) {
+      ey_x = bload<T>(rP, cxn, r0 + 2 * L.sXb);
+      ez_x = bload<T>(rP, cxn, r0 + 3 * L.sXb);
+      kn = bload<T>(rX, o, x0 + AX_KN * L.LAb);
+      an = bload<T>(rX, o, x0 + AX_AN * L.LAb);
+    }
+    if (nxr && tid == 63) {
+      ey_xr = bload<T>(rP, (uint32_t)lxr * sz, r0 + 2 * L.sXb);
+      ez_xr = bload<T>(rP, (uint32_t)lxr * sz, r0 + 3 * L.sXb);
+    }
+  }
+  int lo = 0, hi = 0;
+  if constexpr (ENT) entry_slice_at(A, b, 0, tid, lo, hi);
+  // own H multipliers: the deferred update of their memory
+  const T dtmu = L.dtmu;
+  if constexpr (YZ) {
+    if (py) {
+      bstore<false>(yj.bh * (-dtmu * hx + p_hx_y), rP, o, rowY(ly));
+      bstore<false>(yj.bh * (dtmu * hz + p_hz_y), rP, o, rowY(ly) + L.sYb);
+    }
+    if (pz) {
+      bstore<false>(zk.bh * (dtmu * hx + p_hx_z), rP, o, rowZ(lz));
+      bstore<false>(zk.bh * (-dtmu * hy + p_hy_z), rP, o, rowZ(lz) + L.sZb);
+    }
+  }
+  if constexpr (XL) {
+    if (px) {
+      bstore<false>(bh * (dtmu * hy + p_hy_x), rP, cxh, r0);
+      bstore<false>(bh * (-dtmu * hz + p_hz_x), rP, cxh, r0 + L.sXb);
+    }
+  }
+  // aD / hd of the E differences (edges that are not updated: dt/eps is zero)
+  const T vx = cx * ax, vy = cy * ay, vz = cz * az;
+  const T x1 = td_ad<YZ>(vx, yj.ihd, nyj, ex_yj, yj.kn, yj.an);                    // E_x d1 at j
+  const T x1p = td_ad<YZ>(cx_j * ax_j, yp.ihd, nyp, ex_yp, yp.kn, yp.an);          // at j + 1
+  const T x2 = td_ad<YZ>(-vx, zk.ihd, nzk, ex_zk, zk.kn, zk.an);                   // E_x d2 at k
+  const T x2p = td_ad<YZ>(-(cx_k * ax_k), zp.ihd, nzp, ex_zp, zp.kn, zp.an);       // at k + 1
+  const T y1 = td_ad<YZ>(vy, zk.ihd, nzk, ey_zk, zk.kn, zk.an);                    // E_y d1 at k
+  const T y1p = td_ad<YZ>(cy_k * ay_k, zp.ihd, nzp, ey_zp, zp.kn, zp.an);
+  const T y2 = td_ad<XL>(-vy, ihd, nx0, ey_x, kn, an);                             // E_y d2 at i
+  const T z1 = td_ad<XL>(vz, ihd, nx0, ez_x, kn, an);                              // E_z d1 at i
+  const T z2 = td_ad<YZ>(-vz, yj.ihd, nyj, ez_yj, yj.kn, yj.an);                   // E_z d2 at j
+  const T z2p = td_ad<YZ>(-(cz_j * az_j), yp.ihd, nyp, ez_yp, yp.kn, yp.an);
+  const T y2r = td_ad<XL>(-(cy_r * ay_r), xr.ihd, nxr, ey_xr, xr.kn, xr.an);
+  const T z1r = td_ad<XL>(cz_r * az_r, xr.ihd, nxr, ez_xr, xr.kn, xr.an);
+  const T y2p = lane_above(y2r, y2), z1p = lane_above(z1r, z1);
+  T nhz = hz + (x1 - x1p + y2 - y2p);
+  T nhy = hy + (x2 - x2p + z1 - z1p);
+  T nhx = hx + (y1 - y1p + z2 - z2p);
+  if constexpr (ENT)
+    for (int e = lo; e < hi; ++e) {
+      const int2 en = A.tl_ent[e];
+      if ((en.x & 7) != 7) continue;                        // H receiver nodes
+      const int c = A.rn_c[en.y];
+      if (c == 3) nhx = td_sens_of(A, C, z, s, en.y, nhx);
+      if (c == 4) nhy = td_sens_of(A, C, z, s, en.y, nhy);
+      if (c == 5) nhz = td_sens_of(A, C, z, s, en.y, nhz);
+    }
+  bstore<false>(nhx, rO, o, q + 3 * Fb);
+  bstore<false>(nhy, rO, o, q + 4 * Fb);
+  bstore<false>(nhz, rO, o, q + 5 * Fb);
+}
+
+template <typename T, bool XL, bool YZ, bool ENT>
+__device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int i0,
+                                          int j, int k, const T *Enew, const T *Eold, const double *tdw,
+                                          const double2 *C, const double2 *z) {
+  const bool j_lo = !YZ || j >= 1, k_lo = !YZ || k >= 1, left = !XL || i0 > 0;
+  const int jm = j_lo ? j - 1 : j, km = k_lo ? k - 1 : k;
+  const AxRow<T> yj = L.axr[L.LA + j], ym = L.axr[L.LA + jm], zk = L.axr[2 * L.LA + k],
+                 zm = L.axr[2 * L.LA + km], xl = L.axr[left ? i0 - 1 : 0];
+  asm volatile("; tdh %0" ::"n"(XL * 4 + YZ * 2 + ENT));   // see leap_wave
+  const int tid = threadIdx.x, i = i0 + tid;
+  const int npml = L.npml, W = 2 * npml;
+  const uint32_t sz = sizeof(T), x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
+  const uint32_t q = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0;
+  // rows below a wall are replaced by the node's own: their values reach no
+  // stored result
+  const uint32_t qj = j_lo ? q - L.PXb : q, qk = k_lo ? q - L.PLb : q;
+  const bool i_lo = !XL || i >= 1;
+  const bool okx = j_lo && k_lo, oky = i_lo && k_lo, okz = i_lo && j_lo;
+  const __amdgpu_buffer_rsrc_t rA = rsrc_of(L.fi + (int64_t)s * L.F6), rO = rsrc_of(L.fo + (int64_t)s * L.F6),
+                               rC = rsrc_of(L.ce), rX = rsrc_of(L.axt);
+  const T hx = bload<T>(rA, o, q + 3 * Fb), hy = bload<T>(rA, o, q + 4 * Fb), hz = bload<T>(rA, o, q + 5 * Fb);
+  const T hx_j = bload<T>(rA, o, qj + 3 * Fb), hz_j = bload<T>(rA, o, qj + 5 * Fb);
+  const T hx_k = bload<T>(rA, o, qk + 3 * Fb), hy_k = bload<T>(rA, o, qk + 4 * Fb);
+  const T ax = bload<T>(rA, o, q), ay = bload<T>(rA, o, q + Fb), az = bload<T>(rA, o, q + 2 * Fb);
+  const T cx = bload<T>(rC, o, q), cy = bload<T>(rC, o, q + Fb), cz = bload<T>(rC, o, q + 2 * Fb);
+  const T ih = bload<T>(rX, o, x0 + AX_IH * L.LAb);
+  T hy_l = T(0), hz_l = T(0);
+  if (left && tid == 0) {
+    hy_l = bload<T>(rA, o, q + 4 * Fb - sz);
+    hz_l = bload<T>(rA, o, q + 5 * Fb - sz);
+  }
+  // gradient product of the own edges
+  const int64_t e0 = (int64_t)s * (L.F6 >> 1);
+  const __amdgpu_buffer_rsrc_t rN = rsrc_of(Enew + e0), rD = rsrc_of(Eold + e0), rW = rsrc_of(tdw),
+                               rG = rsrc_of(A.gedge + e0);
+  const T n0 = bload<T>(rN, o, q), n1 = bload<T>(rN, o, q + Fb), n2 = bload<T>(rN, o, q + 2 * Fb);
+  const T d0 = bload<T>(rD, o, q), d1 = bload<T>(rD, o, q + Fb), d2 = bload<T>(rD, o, q + 2 * Fb);
+  constexpr uint32_t up = 8 / sizeof(T);                    // byte offsets of the FP64 arrays
+  const uint32_t og = o * up, qg = q * up, Fg = Fb * up;
+  const double w0 = bload<double>(rW, og, qg), w1 = bload<double>(rW, og, qg + Fg),
+               w2 = bload<double>(rW, og, qg + 2 * Fg);
+  const double g0 = bload<double>(rG, og, qg), g1 = bload<double>(rG, og, qg + Fg),
+               g2 = bload<double>(rG, og, qg + 2 * Fg);
+  // ---- layers ----
+  bool hyj = false, hym = false, hzk = false, hzm = false, hx0 = false, hxl = false;   // memory of H
+  bool nyj = false, nzk = false, nx0 = false;                                          // memory of E
+  int lyj = 0, lym = 0, lzk = 0, lzm = 0, lxl = 0, ny = 0, nz = 0;
+  uint32_t cxh = 0, cxn = 0;
+  if constexpr (YZ) {
+    hyj = pml_half(j, L.ny, npml, lyj);
+    hym = j_lo && pml_half(jm, L.ny, npml, lym);
+    hzk = pml_half(k, L.nz, npml, lzk);
+    hzm = k_lo && pml_half(km, L.nz, npml, lzm);
+    nyj = j_lo && pml_int(j, L.ny, npml, ny);
+    nzk = k_lo && pml_int(k, L.nz, npml, nz);
+  }
+  if constexpr (XL) {
+    hx0 = (i < npml) | (i >= L.nx - npml);
+    nx0 = i_lo & ((i < npml) | (i > L.nx - npml));
+    cxh = (uint32_t)(i < npml ? i : i - L.nx + W) * sz;
+    cxn = (uint32_t)(i < npml ? i : i - L.nx + W - 1) * sz;
+    hxl = left && pml_half(i0 - 1, L.nx, npml, lxl);
+  }
+  const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.pe + (int64_t)s * L.psi_src);
+  const uint32_t r0 = (uint32_t)(k * L.NY + j) * (uint32_t)W * sz;
+  const uint32_t oY = L.oYb + x0, oZ = L.oZb + x0;
+  auto rowY = [&](int l) { return oY + (uint32_t)(k * W + l) * L.PXb; };
+  auto rowZ = [&](int l) { return oZ + (uint32_t)(l * L.NY + j) * L.PXb; };
+  T hx_yj = T(0), hz_yj = T(0), hx_ym = T(0), hz_ym = T(0), hx_zk = T(0), hy_zk = T(0), hx_zm = T(0),
+    hy_zm = T(0), hy_x = T(0), hz_x = T(0), hy_xl = T(0), hz_xl = T(0);
+  T ex_y = T(0), ez_y = T(0), ex_z = T(0), ey_z = T(0), ey_x = T(0), ez_x = T(0);
+  T kh = T(0), ah = T(0), bn = T(0);
+  if constexpr (YZ) {
+    if (hyj) {
+      hx_yj = bload<T>(rP, o, rowY(lyj));
+      hz_yj = bload<T>(rP, o, rowY(lyj) + L.sYb);
+    }
+    if (hym) {
+      hx_ym = bload<T>(rP, o, rowY(lym));
+      hz_ym = bload<T>(rP, o, rowY(lym) + L.sYb);
+    }
+    if (hzk) {
+      hx_zk = bload<T>(rP, o, rowZ(lzk));
+      hy_zk = bload<T>(rP, o, rowZ(lzk) + L.sZb);
+    }
+    if (hzm) {
+      hx_zm = bload<T>(rP, o, rowZ(lzm));
+      hy_zm = bload<T>(rP, o, rowZ(lzm) + L.sZb);
+    }
+    if (nyj) {
+      ex_y = bload<T>(rP, o, rowY(ny) + 2 * L.sYb);
+      ez_y = bload<T>(rP, o, rowY(ny) + 3 * L.sYb);
+    }
+    if (nzk) {
+      ex_z = bload<T>(rP, o, rowZ(nz) + 2 * L.sZb);
+      ey_z = bload<T>(rP, o, rowZ(nz) + 3 * L.sZb);
+    }
+  }
+  if constexpr (XL) {
+    if (hx0) {
+      hy_x = bload<T>(rP, cxh, r0);
+      hz_x = bload<T>(rP, cxh, r0 + L.sXb);
+      kh = bload<T>(rX, o, x0 + AX_KH * L.LAb);
+      ah = bload<T>(rX, o, x0 + AX_AH * L.LAb);
+    }
+    if (hxl && tid == 0) {
+      hy_xl = bload<T>(rP, (uint32_t)lxl * sz, r0);
+      hz_xl = bload<T>(rP, (uint32_t)lxl * sz, r0 + L.sXb);
+    }
+    if (nx0) {
+      ey_x = bload<T>(rP, cxn, r0 + 2 * L.sXb);
+      ez_x = bload<T>(rP, cxn, r0 + 3 * L.sXb);
+      bn = bload<T>(rX, o, x0 + AX_BN * L.LAb);
+    }
+  }
+  int lo = 0, hi = 0;
+  if constexpr (ENT) entry_slice_at(A, b, 0, tid, lo, hi);
+  // own E multipliers: the deferred update of their memory, and the product
+  const T vx = cx * ax, vy = cy * ay, vz = cz * az;
+  if constexpr (YZ) {
+    if (nyj) {
+      if (okx) bstore<false>(yj.bn * (vx + ex_y), rP, o, rowY(ny) + 2 * L.sYb);
+      if (okz) bstore<false>(yj.bn * (-vz + ez_y), rP, o, rowY(ny) + 3 * L.sYb);
+    }
+    if (nzk) {
+      if (okx) bstore<false>(zk.bn * (-vx + ex_z), rP, o, rowZ(nz) + 2 * L.sZb);
+      if (oky) bstore<false>(zk.bn * (vy + ey_z), rP, o, rowZ(nz) + 3 * L.sZb);
+    }
+  }
+  if constexpr (XL) {
+    if (nx0) {
+      if (oky) bstore<false>(bn * (-vy + ey_x), rP, cxn, r0 + 2 * L.sXb);
+      if (okz) bstore<false>(bn * (vz + ez_x), rP, cxn, r0 + 3 * L.sXb);
+    }
+  }
+  if (okx) bstore<false>(g0 + (double)ax * ((double)n0 - (double)d0) * w0, rG, og, qg);
+  if (oky) bstore<false>(g1 + (double)ay * ((double)n1 - (double)d1) * w1, rG, og, qg + Fg);
+  if (okz) bstore<false>(g2 + (double)az * ((double)n2 - (double)d2) * w2, rG, og, qg + 2 * Fg);
+  // aD / h of the H differences: d1 multiplier -dt/mu aH, d2 +dt/mu aH
+  const T dtmu = L.dtmu;
+  const T x1 = td_ad<YZ>(-dtmu * hx, yj.ih, hyj, hx_yj, yj.kh, yj.ah);             // H_x d1 at j
+  const T x1m = td_ad<YZ>(-dtmu * hx_j, ym.ih, hym, hx_ym, ym.kh, ym.ah);          // at j - 1
+  const T x2 = td_ad<YZ>(dtmu * hx, zk.ih, hzk, hx_zk, zk.kh, zk.ah);              // H_x d2 at k
+  const T x2m = td_ad<YZ>(dtmu * hx_k, zm.ih, hzm, hx_zm, zm.kh, zm.ah);
+  const T y1 = td_ad<YZ>(-dtmu * hy, zk.ih, hzk, hy_zk, zk.kh, zk.ah);             // H_y d1 at k
+  const T y1m = td_ad<YZ>(-dtmu * hy_k, zm.ih, hzm, hy_zm, zm.kh, zm.ah);
+  const T y2 = td_ad<XL>(dtmu * hy, ih, hx0, hy_x, kh, ah);                        // H_y d2 at i
+  const T z1 = td_ad<XL>(-dtmu * hz, ih, hx0, hz_x, kh, ah);                       // H_z d1 at i
+  const T z2 = td_ad<YZ>(dtmu * hz, yj.ih, hyj, hz_yj, yj.kh, yj.ah);              // H_z d2 at j
+  const T z2m = td_ad<YZ>(dtmu * hz_j, ym.ih, hym, hz_ym, ym.kh, ym.ah);
+  const T y2l = td_ad<XL>(dtmu * hy_l, xl.ih, hxl, hy_xl, xl.kh, xl.ah);
+  const T z1l = td_ad<XL>(-dtmu * hz_l, xl.ih, hxl, hz_xl, xl.kh, xl.ah);
+  const T y2m = lane_below(y2l, y2), z1m = lane_below(z1l, z1);
+  T nx_ = ax + (y1m - y1 + z2m - z2);
+  T ny_ = ay + (x2m - x2 + z1m - z1);
+  T nz_ = az + (x1m - x1 + y2m - y2);
+  if constexpr (ENT)
+    for (int e = lo; e < hi; ++e) {
+      const int2 en = A.tl_ent[e];
+      const int c = en.x & 3;
+      if (!(en.x & 4) || c == 3) continue;                  // E receiver nodes
+      if (c == 0) nx_ = td_sens_of(A, C, z, s, en.y, nx_);
+      if (c == 1) ny_ = td_sens_of(A, C, z, s, en.y, ny_);
+      if (c == 2) nz_ = td_sens_of(A, C, z, s, en.y, nz_);
+    }
+  if (okx) bstore<false>(nx_, rO, o, q);
+  if (oky) bstore<false>(ny_, rO, o, q + Fb);
+  if (okz) bstore<false>(nz_, rO, o, q + 2 * Fb);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(64) k_rows_td_e(LeapArgs<T> L, StepArgs<T> A, const double2 *C,
+                                                  const double2 *z) {
+  int bx, j, k, s;
+  const int b = tile_of(L, bx, j, k, s);
+  const int i0 = bx * 64;
+  if (i0 + (int)threadIdx.x >= L.nx) return;
+  bool xl, yz;
+  row_kind(L, i0, j, k, xl, yz);
+  // z: null where no magnetic receiver is recorded
+  if (z && j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1)
+    td_e_wave<T, true, true, true>(L, A, s, b, i0, j, k, C, z);
+  else if (xl) {
+    if (yz) td_e_wave<T, true, true, false>(L, A, s, b, i0, j, k, C, z);
+    else td_e_wave<T, true, false, false>(L, A, s, b, i0, j, k, C, z);
+  } else {
+    if (yz) td_e_wave<T, false, true, false>(L, A, s, b, i0, j, k, C, z);
+    else td_e_wave<T, false, false, false>(L, A, s, b, i0, j, k, C, z);
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(64) k_rows_td_h(LeapArgs<T> L, StepArgs<T> A, const T *Enew, const T *Eold,
+                                                  const double *tdw, const double2 *C, const double2 *z) {
+  int bx, j, k, s;
+  const int b = tile_of(L, bx, j, k, s);
+  const int i0 = bx * 64;
+  if (i0 + (int)threadIdx.x >= L.nx) return;
+  bool xl, yz;
+  row_kind(L, i0, j, k, xl, yz);
+  // z: null at the first step (no sample before it)
+  if (z && j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1)
+    td_h_wave<T, true, true, true>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
+  else if (xl) {
+    if (yz) td_h_wave<T, true, true, false>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
+    else td_h_wave<T, true, false, false>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
+  } else {
+    if (yz) td_h_wave<T, false, true, false>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
+    else td_h_wave<T, false, false, false>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
   }
 }
 
@@ -3666,9 +4069,11 @@ static void launch_step(const StepArgs<T> &A, bool hist, dim3 grid, dim3 block, 
 }
 
 // n: the step (the host's count); past the run's last step nothing is
-// injected, recorded or kept
+// injected, recorded or kept.  keep: E^{n+1} of every source also goes there,
+// [ns][3][F] (runs without a volume transform)
 template <typename T>
-static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool adj, int n) {
+static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool adj, int n,
+                             T *keep = nullptr) {
   LeapArgs<T> L{};
   L.fi = A.fields + ((n & 1) ? A.fbuf : 0);
   L.fo = A.fields + ((n & 1) ? 0 : A.fbuf);
@@ -3721,13 +4126,17 @@ static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bo
   const int D = adj ? 1 : p.dec, m = n + 1, r = m / D & (p.kb - 1);
   const bool hist = vol && n < p.nt && m % D == 0 && r != 0;
   if (hist) L.hist = A.hist + (int64_t)(r - 1) * 3 * A.F;
+  if (keep) {
+    L.hist = keep;
+    L.hist_src = 3 * A.F;
+  }
   return L;
 }
 
 template <typename T>
 static void launch_leap(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool adj, int n,
-                        hipStream_t st, const KTime *kt) {
-  const LeapArgs<T> L = leap_args<T>(p, d, A, vol, adj, n);
+                        hipStream_t st, const KTime *kt, T *keep) {
+  const LeapArgs<T> L = leap_args<T>(p, d, A, vol, adj, n, keep);
   const bool hist = L.hist != nullptr;
   const dim3 grid(A.nblocks), block(64);
   if (A.nts) {
@@ -3768,9 +4177,10 @@ static void launch_h(const StepArgs<T> &A, int vx, dim3 grid, dim3 block, hipStr
 // nullptr, ev[0..1] time the H kernel, ev[2..3] the E kernel (one launch or
 // fused: the one kernel in ev[2..3], ev[0..1] recorded back to back) and ev[4..5] the block
 // transform (recorded back to back when there is none); *closed says which.
+// keep: see leap_args (rows of waves only).
 template <typename T>
 static void enqueue_step(Plan &p, Dev &d, const WS &w, void *vol, bool adj, hipStream_t st,
-                         hipEvent_t *ev, int r, int n, bool *closed = nullptr) {
+                         hipEvent_t *ev, int r, int n, bool *closed = nullptr, T *keep = nullptr) {
   StepArgs<T> A = make_args<T>(p, d, w, vol, adj, r);
   const dim3 block(p.bx, p.by), grid(A.nblocks);
   const KTime th_ev = ev ? KTime{ev[0], ev[1]} : KTime{}, te_ev = ev ? KTime{ev[2], ev[3]} : KTime{};
@@ -3792,7 +4202,7 @@ static void enqueue_step(Plan &p, Dev &d, const WS &w, void *vol, bool adj, hipS
       (void)hipEventRecord(ev[1], st);
     }
     const Tiling t = tiling(p);
-    launch_leap<T>(p, d, A, vol != nullptr, adj, n, st, ke);
+    launch_leap<T>(p, d, A, vol != nullptr, adj, n, st, ke, keep);
   } else if (p.sched == 1) {
     if (ev) {
       (void)hipEventRecord(ev[0], st);
@@ -3815,7 +4225,7 @@ static void enqueue_step(Plan &p, Dev &d, const WS &w, void *vol, bool adj, hipS
     Ah.tl_ent = hinj ? d.tl_ent[hm] : nullptr;
     const bool o4 = p.fd_order == 4;
     if (o4 && wave_rows(p)) {
-      const LeapArgs<T> L = leap_args<T>(p, d, A, vol != nullptr, adj, n);
+      const LeapArgs<T> L = leap_args<T>(p, d, A, vol != nullptr, adj, n, keep);
       const dim3 row(64);
       if (hinj && n < p.nt) go(k_rows_h4<T, true>, grid, row, 0, st, kh, L, Ah);
       else go(k_rows_h4<T, false>, grid, row, 0, st, kh, L, Ah);
@@ -4440,11 +4850,41 @@ static void adjoint_td_t(Plan &p, Dev &d, const WS &w, void *ws, char *scratch, 
   double *tdw = reinterpret_cast<double *>(b);
   HIP_CHECK(hipMemcpyAsync(coef, C.data(), C.size() * sizeof(double), hipMemcpyHostToDevice, st));
   HIP_CHECK(hipMemcpyAsync(tdw, Wt.data(), Wt.size() * sizeof(double), hipMemcpyHostToDevice, st));
-  // forward run, checkpointing the core state at the start of every segment
+  T *fields = static_cast<T *>(w.fields);
+  const int64_t fbuf = (int64_t)ns * 6 * F, eslice = (int64_t)ns * 3 * F;
+  const int cgrid = (int)std::min<int64_t>(((int64_t)ns * 3 * F + 255) / 256, 65536);
+  auto copy_e = [&](int t, int half) {
+    hipLaunchKernelGGL((k_copy_e<T>), dim3(cgrid), dim3(256), 0, st, eseg + t * eslice, fields, fbuf,
+                       half, ns, F);
+  };
+  // the len steps from n0 on, keeping E^{n0} .. E^{n0+len} in eseg: rows of
+  // waves store it with the step (a copy after each took 6.8 us on the marine
+  // grid, of 22 us a step), the general kernels' is copied
+  const bool keep = wave_rows(p);
+  auto segment = [&](int n0, int len) {
+    hipLaunchKernelGGL(k_equalize, dim3(1), dim3(64), 0, st, w.step);
+    copy_e(0, n0 & 1);
+    int r = 0;
+    for (int t = 1; t <= len; ++t) {
+      enqueue_step<T>(p, d, w, nullptr, false, st, nullptr, r, n0 + t - 1, nullptr,
+                      keep ? eseg + t * eslice : nullptr);
+      r ^= 1;
+      if (!keep) copy_e(t, (n0 + t) & 1);
+    }
+  };
+  // forward run, checkpointing the core state at the start of every segment;
+  // the last one is kept at once where no kernel times are sampled
   zero_state(p, w, ws, FWD_MODE_FORWARD, st);
+  const bool last_kept = d.sample_every <= 0 && p.sched != 2;
   for (int sg = 0; sg < nseg; ++sg) {
+    const int n0 = sg * L, len = std::min(L, nt - n0);
+    if (last_kept && sg == nseg - 1) {
+      segment(n0, len);
+      p.host_step = nt;
+      break;
+    }
     HIP_CHECK(hipMemcpyAsync(ckpt + (size_t)sg * ckb, ws, core, hipMemcpyDeviceToDevice, st));
-    run_steps_t<T>(p, d, w, nullptr, false, std::min(L, nt - sg * L), st);
+    run_steps_t<T>(p, d, w, nullptr, false, len, st);
   }
   // adjoint state at zero; the sensitivity to the last sample E^nt
   HIP_CHECK(hipMemsetAsync(afld, 0, afld_b, st));
@@ -4461,9 +4901,7 @@ static void adjoint_td_t(Plan &p, Dev &d, const WS &w, void *ws, char *scratch, 
   A.psi = apsi;
   A.pbuf = 0;
   A.gedge = gedge;
-  const dim3 block(p.bx, p.by), grid(A.nblocks);
-  const dim3 sgrid((ns * nn + 127) / 128), sblock(128);
-  const int cgrid = (int)std::min<int64_t>(((int64_t)ns * 3 * F + 255) / 256, 65536);
+  const dim3 block(p.bx, p.by), sgrid((ns * nn + 127) / 128), sblock(128);
   auto sens = [&](int m) {
     hipLaunchKernelGGL((k_td_sens<T>), sgrid, sblock, 0, st, afld, F, ns, nn, nf, d.rn_c, d.rn_idx,
                        coef, d.zE + (int64_t)(m - 1) * nf, 0);
@@ -4471,31 +4909,40 @@ static void adjoint_td_t(Plan &p, Dev &d, const WS &w, void *ws, char *scratch, 
   // magnetic receivers: d phi / d H^{n+1/2} joins the H multipliers after
   // k_td_e (whose deferred CPML update still needs the previous value) and
   // before k_td_h reads them
+  const bool rows = one_launch(p);
+  LeapArgs<T> R{};
+  if (rows) {
+    const Tiling t = tiling(p);
+    set_grid(A, t.nbx, t.nby, t.nbz);
+    A.tile_tab = d.tile_tab[1];
+    A.tl_off = d.tl_off[1];
+    A.tl_ent = d.tl_ent[1];
+    R = leap_args<T>(p, d, A, false, true, 0);
+  }
   auto hsens = [&](int n) {
     if (d.nh > 0)
       hipLaunchKernelGGL((k_td_sens<T>), sgrid, sblock, 0, st, afld, F, ns, nn, nf, d.rn_c,
                          d.rn_idx, coef, d.zH + (int64_t)n * nf, 1);
   };
   sens(nt);
-  T *fields = static_cast<T *>(w.fields);
-  const int64_t fbuf = (int64_t)ns * 6 * F, eslice = (int64_t)ns * 3 * F;
+  const dim3 grid(A.nblocks), row(64);
   for (int sg = nseg - 1; sg >= 0; --sg) {
     const int n0 = sg * L, len = std::min(L, nt - n0);
-    // replay the segment from its checkpoint, keeping E^{n0} .. E^{n0+len}
-    HIP_CHECK(hipMemcpyAsync(ws, ckpt + (size_t)sg * ckb, core, hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(k_equalize, dim3(1), dim3(64), 0, st, w.step);
-    hipLaunchKernelGGL((k_copy_e<T>), dim3(cgrid), dim3(256), 0, st, eseg, fields, fbuf, n0 & 1, ns,
-                       F);
-    int r = 0;
-    for (int t = 1; t <= len; ++t) {
-      enqueue_step<T>(p, d, w, nullptr, false, st, nullptr, r, n0 + t - 1);
-      r ^= 1;
-      hipLaunchKernelGGL((k_copy_e<T>), dim3(cgrid), dim3(256), 0, st, eseg + t * eslice, fields,
-                         fbuf, (n0 + t) & 1, ns, F);
+    if (!last_kept || sg < nseg - 1) {   // replay the segment from its checkpoint
+      HIP_CHECK(hipMemcpyAsync(ws, ckpt + (size_t)sg * ckb, core, hipMemcpyDeviceToDevice, st));
+      segment(n0, len);
     }
     // reverse steps n0 + len - 1 .. n0
     for (int n = n0 + len - 1; n >= n0; --n) {
       const int t = n - n0;
+      if (rows) {
+        const double2 *zh = d.nh > 0 ? d.zH + (int64_t)n * nf : nullptr;
+        const double2 *ze = n >= 1 ? d.zE + (int64_t)(n - 1) * nf : nullptr;
+        hipLaunchKernelGGL((k_rows_td_e<T>), grid, row, 0, st, R, A, coef, zh);
+        hipLaunchKernelGGL((k_rows_td_h<T>), grid, row, 0, st, R, A, eseg + (t + 1) * eslice,
+                           eseg + t * eslice, (const double *)tdw, coef, ze);
+        continue;
+      }
       if (p.fd_order == 4) {
         hipLaunchKernelGGL((k_td_e<T, 4>), grid, block, 0, st, A);
         hsens(n);
