@@ -940,7 +940,7 @@ k_update_e_s(StepArgs<float> A) {
 // differences E edges on the wall), and E there is never updated.
 //
 // Measured a step, two kernels -> this (one MI355X): 101x101x61 FP32, 30.1 ->
-// 17.3 us; the same with 4 sources 77.2 -> 47.5 us; 200x200x100, 8 sources,
+// 16.9 us; the same with 4 sources 77.2 -> 47.5 us; 200x200x100, 8 sources,
 // 943 -> 628 us (3.9 TB/s of the bytes it cannot do without); FP64
 // 128x128x96 113 -> 85 us.  Not kept: 2 nodes a lane
 // (FP32; 20.5 us on the marine grid), a march in z with H of the plane below
@@ -1043,14 +1043,101 @@ struct LeapArgs {
   int lean;
   int nbx, nby, nbz, nblocks, xcd, order, ns;
   FDiv dns, dnbx, dnby, dnbz;
-  const int *tile_tab;
+  // injections and receivers by row (see build_rows): of each block's row its
+  // receiver table and its source table, or -1
+  const int2 *row_tab;
+  const int *row_rec;                // [tables][6][64] receiver node of the lane's component, or -1
+  const int *row_src;                // [tables][ns][3][64] first coefficient of its injection, or -1
+  int rec_mask;                      // components that have receiver nodes at all (Ex .. Hz)
+  int adj;                           // adjoint run: the E receiver nodes are the injections
   int ej0, ej1, ek0, ek1;            // rows and planes that hold entries (empty: j1 < j0)
 };
 
+// The lane's receiver nodes and injections.  A lane has at most one of each a
+// component, so they come as rows of lanes: the loads of all components, then
+// those of all their coefficients or sums, are in flight together.  A list a
+// lane (an offset, the entries, for each its coefficients, sums and twiddles,
+// one after the other) made the waves that hold entries the longest of the
+// launch.  Measured, lists -> rows, FP64 gradient of 14x12x10 cells 9.2 -> 5.5
+// ms over 800 steps (4.1 without any entry), data of 32x32x32 cells 4.2 -> 2.9
+// ms over 512; FP32 gradient of 101x101x61 cells 22.2 -> 21.7 ms.
+struct RowEnt {
+  int node[6], src[3];
+};
+template <typename T>
+__device__ __forceinline__ RowEnt row_entries(const LeapArgs<T> &L, const StepArgs<T> &A, int2 tt, int s,
+                                              int tid) {
+  RowEnt e;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    e.node[c] = -1;
+    if (tt.x >= 0 && (L.rec_mask >> c & 1)) e.node[c] = L.row_rec[(tt.x * 6 + c) * 64 + tid];
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    e.src[c] = -1;
+    if (L.adj) e.src[c] = e.node[c] >= 0 ? (s * A.nn + e.node[c]) * A.nrow : -1;
+    else if (tt.y >= 0) e.src[c] = L.row_src[((tt.y * L.ns + s) * 3 + c) * 64 + tid];
+  }
+  return e;
+}
+
+// injected currents of the lane's edges at step n (the sums of inject_all)
+template <typename T>
+__device__ __forceinline__ void inject_row(const StepArgs<T> &A, const RowEnt &e, int n, double (&inj)[3]) {
+  inj[0] = inj[1] = inj[2] = 0.0;
+  if (max(e.src[0], max(e.src[1], e.src[2])) < 0) return;
+  const double *cf[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) cf[c] = A.coef + max(e.src[c], 0);
+#pragma unroll 2
+  for (int r = 0; r < A.nrow; ++r) {
+    const double f = A.Ftab[(int64_t)r * A.nt + n];
+    double k[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) k[c] = cf[c][r];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) inj[c] = e.src[c] >= 0 ? fma(k[c], f, inj[c]) : inj[c];
+  }
+}
+
+// receiver transforms of the lane's nodes of the components C .. C + 2, twiddles z
+template <int C, typename T>
+__device__ __forceinline__ void record_row(const StepArgs<T> &A, const RowEnt &e, int s, const double2 *z,
+                                           const double (&v)[3]) {
+  if (max(e.node[C], max(e.node[C + 1], e.node[C + 2])) < 0) return;
+  double2 *__restrict__ a[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) a[c] = A.racc + ((int64_t)s * A.nn + max(e.node[C + c], 0)) * A.nf;
+#pragma unroll 2
+  for (int kf = 0; kf < A.nf; ++kf) {
+    const double2 w = z[kf];
+    double2 x[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) x[c] = a[c][kf];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      x[c].x = fma(v[c], w.x, x[c].x);
+      x[c].y = fma(v[c], w.y, x[c].y);
+      if (e.node[C + c] >= 0) a[c][kf] = x[c];
+    }
+  }
+}
+
+// The tables of a row with entries.  The kernel has read them to choose the
+// variant; FP32 reads them again, because kept over the choice they took 25
+// registers more (140: three waves a SIMD for four, 101x101x61 with 4 sources
+// 13.5 ms against 12.3), while FP64 stays at two waves either way.
+template <typename T, bool ENT>
+__device__ __forceinline__ int2 own_row(const LeapArgs<T> &L, int b, int2 row) {
+  if constexpr (ENT && sizeof(T) == 4) return L.row_tab[b];
+  return row;
+}
+
 // XL: nodes of the wave may lie in an x layer or at an x wall; YZ: the row
-// may lie in a y or z layer or at a wall; ENT: it may hold entries.
+// may lie in a y or z layer or at a wall; ENT: it holds entries (row: its tables).
 template <typename T, bool HIST, bool NT, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b,
+__device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int2 row,
                                           int i0, int j, int k) {
   // coefficients of the rows j, j - 1, k, k - 1 and of i0 - 1: read before
   // the marker below, so that they are scalar loads
@@ -1058,6 +1145,8 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   const int jm = j_lo ? j - 1 : j, km = k_lo ? k - 1 : k;
   const AxRow<T> yj = L.axr[L.LA + j], ym = L.axr[L.LA + jm], zk = L.axr[2 * L.LA + k],
                  zm = L.axr[2 * L.LA + km], xl = L.axr[left ? i0 - 1 : 0];
+  const int2 tt = own_row<T, ENT>(L, b, row);
+  const int n = ENT ? L.step[0] + 1 : 0;
   // each variant starts with its own marker: loads common to the variants
   // are not hoisted above the branches (that kept the registers of all of
   // them alive at once)
@@ -1066,6 +1155,8 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T);
   const bool i_lo = !XL || i >= 1;
+  RowEnt ent;
+  if constexpr (ENT) ent = row_entries(L, A, tt, s, tid);
   // rows below a wall are replaced by the node's own: their values reach no
   // stored result
   const uint32_t dj = L.PXb, ej = j_lo ? 0u - L.PXb : 0u;
@@ -1108,7 +1199,6 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   }
   const T cx = bload<T>(rC, o, x), cy = bload<T>(rC, o, y), cz = bload<T>(rC, o, z);
   const T ih = bload<T>(rX, o, x0 + AX_IH * L.LAb), ihd = bload<T>(rX, o, x0 + AX_IHD * L.LAb);
-  const int tt = ENT ? L.tile_tab[b] : -1;
   // ---- layers: slab indices and memory ----
   bool px = false, pxn = false, pxl = false;
   bool py = false, pym = false, pyn = false, pz = false, pzm = false, pzn = false;
@@ -1199,12 +1289,8 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
       }
     }
   }
-  int lo = 0, hi = 0, n = 0;
-  if (ENT && tt >= 0) {
-    n = L.step[0] + 1;
-    lo = A.tl_off[tt + tid];
-    hi = A.tl_off[tt + tid + 1];
-  }
+  double inj[3];
+  if constexpr (ENT) inject_row(A, ent, n, inj);
   // ---- H^{n+1/2} at the node and, recomputed, at j - 1, k - 1 and i - 1 ----
   const T mc = -L.dtmu;
   const T hj = yj.ih, hjm = ym.ih, hk = zk.ih, hkm = zm.ih;
@@ -1234,9 +1320,7 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   T e1x = curl_update<YZ, YZ>(ex0, cx, Hz, Hzj, yj.ihd, pyn, ex_y, yn, Hy, Hyk, zk.ihd, pzn, ex_z, zn);
   T e1y = curl_update<YZ, XL>(ey0, cy, Hx, Hxk, zk.ihd, pzn, ey_z, zn, Hz, Hzi, ihd, pxn, ey_x, xn);
   T e1z = curl_update<XL, YZ>(ez0, cz, Hy, Hyi, ihd, pxn, ez_x, xn, Hx, Hxj, yj.ihd, pyn, ez_y, yn);
-  if (ENT && lo < hi) {
-    double inj[3];
-    inject_all<T, 1>(A, lo, hi, s, n, inj);
+  if constexpr (ENT) {
     e1x -= (T)((double)cx * inj[0]);
     e1y -= (T)((double)cy * inj[1]);
     e1z -= (T)((double)cz * inj[2]);
@@ -1245,6 +1329,11 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   if constexpr (XL) {
     e1y = i_lo ? e1y : ey0;
     e1z = i_lo ? e1z : ez0;
+  }
+  if constexpr (ENT) {                   // before the stores: the sums' loads would wait for them
+    const double e1[3] = {(double)e1x, (double)e1y, (double)e1z}, h1[3] = {(double)Hx, (double)Hy, (double)Hz};
+    record_row<0>(A, ent, s, A.zE + (int64_t)n * A.nf, e1);
+    if (L.rec_mask >> 3) record_row<3>(A, ent, s, A.zH + (int64_t)n * A.nf, h1);
   }
   // ---- stores ----
   const bool row_x = j_lo && k_lo, row_y = k_lo, row_z = j_lo;
@@ -1293,12 +1382,6 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
       }
     }
   }
-  if (ENT && lo < hi) {
-    const Vec<T, 1> e1[3] = {vec1(e1x), vec1(e1y), vec1(e1z)};
-    const unsigned ok[3] = {row_x ? 1u : 0u, i_lo && row_y ? 1u : 0u, i_lo && row_z ? 1u : 0u};
-    const Vec<T, 1> hh[3] = {vec1(Hx), vec1(Hy), vec1(Hz)};
-    record_all<T, 1>(A, lo, hi, s, n, e1, ok, hh);
-  }
 }
 
 template <typename T, bool HIST, bool NT>
@@ -1311,14 +1394,16 @@ __global__ void __launch_bounds__(64) k_leap(LeapArgs<T> L, StepArgs<T> A) {
   const int np = L.npml;
   const bool xl = !L.lean || i0 <= np || i0 + 64 > L.nx - np;
   const bool yz = !L.lean || j <= np || j >= L.ny - np || k <= np || k >= L.nz - np;
-  if (j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1)
-    leap_wave<T, HIST, NT, true, true, true>(L, A, s, b, i0, j, k);
+  int2 row = make_int2(-1, -1);   // rows outside the box of the entries do not ask
+  if (j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1) row = L.row_tab[b];
+  if (max(row.x, row.y) >= 0)
+    leap_wave<T, HIST, NT, true, true, true>(L, A, s, b, row, i0, j, k);
   else if (xl) {
-    if (yz) leap_wave<T, HIST, NT, true, true, false>(L, A, s, b, i0, j, k);
-    else leap_wave<T, HIST, NT, true, false, false>(L, A, s, b, i0, j, k);
+    if (yz) leap_wave<T, HIST, NT, true, true, false>(L, A, s, b, row, i0, j, k);
+    else leap_wave<T, HIST, NT, true, false, false>(L, A, s, b, row, i0, j, k);
   } else {
-    if (yz) leap_wave<T, HIST, NT, false, true, false>(L, A, s, b, i0, j, k);
-    else leap_wave<T, HIST, NT, false, false, false>(L, A, s, b, i0, j, k);
+    if (yz) leap_wave<T, HIST, NT, false, true, false>(L, A, s, b, row, i0, j, k);
+    else leap_wave<T, HIST, NT, false, false, false>(L, A, s, b, row, i0, j, k);
   }
 }
 
@@ -1655,11 +1740,15 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
 }
 
 template <typename T, bool HIST, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int i0,
+__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int2 row, int i0,
                                         int j, int k) {
   const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];
+  const int2 tt = own_row<T, ENT>(L, b, row);
+  const int n = ENT ? L.step[0] + 1 : 0;
   asm volatile("; e4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));
   const int tid = threadIdx.x, i = i0 + tid;
+  RowEnt ent;
+  if constexpr (ENT) ent = row_entries(L, A, tt, s, tid);
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T);
   const uint32_t x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
@@ -1746,11 +1835,8 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
     xn = {bload<T>(rX, o, x0 + AX_BN * L.LAb), bload<T>(rX, o, x0 + AX_AN * L.LAb),
           bload<T>(rX, o, x0 + AX_KN * L.LAb)};
   }
-  int lo = 0, hi = 0, n = 0;
-  if constexpr (ENT) {
-    n = L.step[0] + 1;
-    entry_slice_at(A, b, n, tid, lo, hi);
-  }
+  double inj[3];
+  if constexpr (ENT) inject_row(A, ent, n, inj);
   const T zero = T(0);
   const Stretch<T> yn{yj.bn, yj.an, yj.kn}, zn{zk.bn, zk.an, zk.kn};
   T e1x = curl_update<YZ, YZ>(ex, cx, d4(hz_ja, hz_jb, hz, hz_jd), zero, yj.ihd, pyn, ex_y, yn,
@@ -1759,9 +1845,7 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
                               d4(hz_ia, hz_ib, hz, hz_id), zero, ihd, pxn, ey_x, xn);
   T e1z = curl_update<XL, YZ>(ez, cz, d4(hy_ia, hy_ib, hy, hy_id), zero, ihd, pxn, ez_x, xn,
                               d4(hx_ja, hx_jb, hx, hx_jd), zero, yj.ihd, pyn, ez_y, yn);
-  if (ENT && lo < hi) {
-    double inj[3];
-    inject_all<T, 1>(A, lo, hi, s, n, inj);
+  if constexpr (ENT) {
     e1x -= (T)((double)cx * inj[0]);
     e1y -= (T)((double)cy * inj[1]);
     e1z -= (T)((double)cz * inj[2]);
@@ -1769,6 +1853,11 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   if constexpr (XL) {                    // edges on the low x wall keep their value (zero)
     e1y = i_lo ? e1y : ey;
     e1z = i_lo ? e1z : ez;
+  }
+  if constexpr (ENT) {                   // before the stores: the sums' loads would wait for them
+    const double e1[3] = {(double)e1x, (double)e1y, (double)e1z}, h1[3] = {(double)hx, (double)hy, (double)hz};
+    record_row<0>(A, ent, s, A.zE + (int64_t)n * A.nf, e1);
+    if (L.rec_mask >> 3) record_row<3>(A, ent, s, A.zH + (int64_t)n * A.nf, h1);
   }
   const bool row_x = j_lo && k_lo, row_y = k_lo, row_z = j_lo;
   if (row_x) bstore<false>(e1x, rO, o, q);
@@ -1791,12 +1880,6 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   if (XL && pxn) {
     if (row_y) bstore<false>(ey_x, rE, cxn, r0);
     if (row_z) bstore<false>(ez_x, rE, cxn, r0 + L.sXb);
-  }
-  if (ENT && lo < hi) {
-    const Vec<T, 1> e1[3] = {vec1(e1x), vec1(e1y), vec1(e1z)};
-    const unsigned ok[3] = {row_x ? 1u : 0u, i_lo && row_y ? 1u : 0u, i_lo && row_z ? 1u : 0u};
-    const Vec<T, 1> hh[3] = {vec1(hx), vec1(hy), vec1(hz)};
-    record_all<T, 1>(A, lo, hi, s, n, e1, ok, hh);
   }
 }
 
@@ -1837,14 +1920,16 @@ __global__ void __launch_bounds__(64) k_rows_e4(LeapArgs<T> L, StepArgs<T> A) {
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
-  if (j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1)
-    e4_wave<T, HIST, true, true, true>(L, A, s, b, i0, j, k);
+  int2 row = make_int2(-1, -1);
+  if (j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1) row = L.row_tab[b];
+  if (max(row.x, row.y) >= 0)
+    e4_wave<T, HIST, true, true, true>(L, A, s, b, row, i0, j, k);
   else if (xl) {
-    if (yz) e4_wave<T, HIST, true, true, false>(L, A, s, b, i0, j, k);
-    else e4_wave<T, HIST, true, false, false>(L, A, s, b, i0, j, k);
+    if (yz) e4_wave<T, HIST, true, true, false>(L, A, s, b, row, i0, j, k);
+    else e4_wave<T, HIST, true, false, false>(L, A, s, b, row, i0, j, k);
   } else {
-    if (yz) e4_wave<T, HIST, false, true, false>(L, A, s, b, i0, j, k);
-    else e4_wave<T, HIST, false, false, false>(L, A, s, b, i0, j, k);
+    if (yz) e4_wave<T, HIST, false, true, false>(L, A, s, b, row, i0, j, k);
+    else e4_wave<T, HIST, false, false, false>(L, A, s, b, row, i0, j, k);
   }
 }
 
@@ -2684,25 +2769,39 @@ __device__ __forceinline__ T td_ad(T ad, T h, bool in, T p, T kinv, T a) {
   return v * h;
 }
 
-// -Re sum_k C_k z_k (k_td_sens) of the listed node, added to v
-template <typename T>
-__device__ __forceinline__ T td_sens_of(const StepArgs<T> &A, const double2 *C, const double2 *z, int s,
-                                        int node, T v) {
-  double g = 0.0;
+// -Re sum_k C_k z_k (k_td_sens) of the lane's nodes of the components K ..
+// K + 2, added to v
+template <int K, typename T>
+__device__ __forceinline__ void td_sens_row(const StepArgs<T> &A, const RowEnt &e, const double2 *C,
+                                            const double2 *z, int s, T (&v)[3]) {
+  if (max(e.node[K], max(e.node[K + 1], e.node[K + 2])) < 0) return;
+  const double2 *q[3];
+  double g[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) q[c] = C + ((int64_t)s * A.nn + max(e.node[K + c], 0)) * A.nf;
+#pragma unroll 2
   for (int kf = 0; kf < A.nf; ++kf) {
-    const double2 c = C[((int64_t)s * A.nn + node) * A.nf + kf];
-    g -= c.x * z[kf].x - c.y * z[kf].y;
+    const double2 w = z[kf];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const double2 u = q[c][kf];
+      g[c] -= u.x * w.x - u.y * w.y;
+    }
   }
-  return v + (T)g;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) v[c] = e.node[K + c] >= 0 ? v[c] + (T)g[c] : v[c];
 }
 
 template <typename T, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int i0,
+__device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int2 row, int i0,
                                           int j, int k, const double2 *C, const double2 *z) {
   const AxRow<T> yj = L.axr[L.LA + j], yp = L.axr[L.LA + j + 1], zk = L.axr[2 * L.LA + k],
                  zp = L.axr[2 * L.LA + k + 1], xr = L.axr[min(i0 + 64, L.nx)];
+  const int2 tt = own_row<T, ENT>(L, b, row);
   asm volatile("; tde %0" ::"n"(XL * 4 + YZ * 2 + ENT));   // see leap_wave
   const int tid = threadIdx.x, i = i0 + tid;
+  RowEnt ent;
+  if constexpr (ENT) ent = row_entries(L, A, tt, s, tid);
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T), x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
   const uint32_t q = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0, qj = q + L.PXb, qk = q + L.PLb;
@@ -2799,8 +2898,6 @@ __device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T
       ez_xr = bload<T>(rP, (uint32_t)lxr * sz, r0 + 3 * L.sXb);
     }
   }
-  int lo = 0, hi = 0;
-  if constexpr (ENT) entry_slice_at(A, b, 0, tid, lo, hi);
   // own H multipliers: the deferred update of their memory
   const T dtmu = L.dtmu;
   if constexpr (YZ) {
@@ -2834,33 +2931,26 @@ __device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T
   const T y2r = td_ad<XL>(-(cy_r * ay_r), xr.ihd, nxr, ey_xr, xr.kn, xr.an);
   const T z1r = td_ad<XL>(cz_r * az_r, xr.ihd, nxr, ez_xr, xr.kn, xr.an);
   const T y2p = lane_above(y2r, y2), z1p = lane_above(z1r, z1);
-  T nhz = hz + (x1 - x1p + y2 - y2p);
-  T nhy = hy + (x2 - x2p + z1 - z1p);
-  T nhx = hx + (y1 - y1p + z2 - z2p);
-  if constexpr (ENT)
-    for (int e = lo; e < hi; ++e) {
-      const int2 en = A.tl_ent[e];
-      if ((en.x & 7) != 7) continue;                        // H receiver nodes
-      const int c = A.rn_c[en.y];
-      if (c == 3) nhx = td_sens_of(A, C, z, s, en.y, nhx);
-      if (c == 4) nhy = td_sens_of(A, C, z, s, en.y, nhy);
-      if (c == 5) nhz = td_sens_of(A, C, z, s, en.y, nhz);
-    }
-  bstore<false>(nhx, rO, o, q + 3 * Fb);
-  bstore<false>(nhy, rO, o, q + 4 * Fb);
-  bstore<false>(nhz, rO, o, q + 5 * Fb);
+  T nh[3] = {hx + (y1 - y1p + z2 - z2p), hy + (x2 - x2p + z1 - z1p), hz + (x1 - x1p + y2 - y2p)};
+  if constexpr (ENT) td_sens_row<3>(A, ent, C, z, s, nh);
+  bstore<false>(nh[0], rO, o, q + 3 * Fb);
+  bstore<false>(nh[1], rO, o, q + 4 * Fb);
+  bstore<false>(nh[2], rO, o, q + 5 * Fb);
 }
 
 template <typename T, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int i0,
+__device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int2 row, int i0,
                                           int j, int k, const T *Enew, const T *Eold, const double *tdw,
                                           const double2 *C, const double2 *z) {
   const bool j_lo = !YZ || j >= 1, k_lo = !YZ || k >= 1, left = !XL || i0 > 0;
   const int jm = j_lo ? j - 1 : j, km = k_lo ? k - 1 : k;
   const AxRow<T> yj = L.axr[L.LA + j], ym = L.axr[L.LA + jm], zk = L.axr[2 * L.LA + k],
                  zm = L.axr[2 * L.LA + km], xl = L.axr[left ? i0 - 1 : 0];
+  const int2 tt = own_row<T, ENT>(L, b, row);
   asm volatile("; tdh %0" ::"n"(XL * 4 + YZ * 2 + ENT));   // see leap_wave
   const int tid = threadIdx.x, i = i0 + tid;
+  RowEnt ent;
+  if constexpr (ENT) ent = row_entries(L, A, tt, s, tid);
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T), x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
   const uint32_t q = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0;
@@ -2966,8 +3056,6 @@ __device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T
       bn = bload<T>(rX, o, x0 + AX_BN * L.LAb);
     }
   }
-  int lo = 0, hi = 0;
-  if constexpr (ENT) entry_slice_at(A, b, 0, tid, lo, hi);
   // own E multipliers: the deferred update of their memory, and the product
   const T vx = cx * ax, vy = cy * ay, vz = cz * az;
   if constexpr (YZ) {
@@ -3004,21 +3092,11 @@ __device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T
   const T y2l = td_ad<XL>(dtmu * hy_l, xl.ih, hxl, hy_xl, xl.kh, xl.ah);
   const T z1l = td_ad<XL>(-dtmu * hz_l, xl.ih, hxl, hz_xl, xl.kh, xl.ah);
   const T y2m = lane_below(y2l, y2), z1m = lane_below(z1l, z1);
-  T nx_ = ax + (y1m - y1 + z2m - z2);
-  T ny_ = ay + (x2m - x2 + z1m - z1);
-  T nz_ = az + (x1m - x1 + y2m - y2);
-  if constexpr (ENT)
-    for (int e = lo; e < hi; ++e) {
-      const int2 en = A.tl_ent[e];
-      const int c = en.x & 3;
-      if (!(en.x & 4) || c == 3) continue;                  // E receiver nodes
-      if (c == 0) nx_ = td_sens_of(A, C, z, s, en.y, nx_);
-      if (c == 1) ny_ = td_sens_of(A, C, z, s, en.y, ny_);
-      if (c == 2) nz_ = td_sens_of(A, C, z, s, en.y, nz_);
-    }
-  if (okx) bstore<false>(nx_, rO, o, q);
-  if (oky) bstore<false>(ny_, rO, o, q + Fb);
-  if (okz) bstore<false>(nz_, rO, o, q + 2 * Fb);
+  T ne[3] = {ax + (y1m - y1 + z2m - z2), ay + (x2m - x2 + z1m - z1), az + (x1m - x1 + y2m - y2)};
+  if constexpr (ENT) td_sens_row<0>(A, ent, C, z, s, ne);
+  if (okx) bstore<false>(ne[0], rO, o, q);
+  if (oky) bstore<false>(ne[1], rO, o, q + Fb);
+  if (okz) bstore<false>(ne[2], rO, o, q + 2 * Fb);
 }
 
 template <typename T>
@@ -3031,14 +3109,16 @@ __global__ void __launch_bounds__(64) k_rows_td_e(LeapArgs<T> L, StepArgs<T> A, 
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
   // z: null where no magnetic receiver is recorded
-  if (z && j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1)
-    td_e_wave<T, true, true, true>(L, A, s, b, i0, j, k, C, z);
+  int2 row = make_int2(-1, -1);
+  if (z && j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1) row = L.row_tab[b];
+  if (max(row.x, row.y) >= 0)
+    td_e_wave<T, true, true, true>(L, A, s, b, row, i0, j, k, C, z);
   else if (xl) {
-    if (yz) td_e_wave<T, true, true, false>(L, A, s, b, i0, j, k, C, z);
-    else td_e_wave<T, true, false, false>(L, A, s, b, i0, j, k, C, z);
+    if (yz) td_e_wave<T, true, true, false>(L, A, s, b, row, i0, j, k, C, z);
+    else td_e_wave<T, true, false, false>(L, A, s, b, row, i0, j, k, C, z);
   } else {
-    if (yz) td_e_wave<T, false, true, false>(L, A, s, b, i0, j, k, C, z);
-    else td_e_wave<T, false, false, false>(L, A, s, b, i0, j, k, C, z);
+    if (yz) td_e_wave<T, false, true, false>(L, A, s, b, row, i0, j, k, C, z);
+    else td_e_wave<T, false, false, false>(L, A, s, b, row, i0, j, k, C, z);
   }
 }
 
@@ -3052,14 +3132,16 @@ __global__ void __launch_bounds__(64) k_rows_td_h(LeapArgs<T> L, StepArgs<T> A, 
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
   // z: null at the first step (no sample before it)
-  if (z && j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1)
-    td_h_wave<T, true, true, true>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
+  int2 row = make_int2(-1, -1);
+  if (z && j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1) row = L.row_tab[b];
+  if (max(row.x, row.y) >= 0)
+    td_h_wave<T, true, true, true>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
   else if (xl) {
-    if (yz) td_h_wave<T, true, true, false>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
-    else td_h_wave<T, true, false, false>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
+    if (yz) td_h_wave<T, true, true, false>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
+    else td_h_wave<T, true, false, false>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
   } else {
-    if (yz) td_h_wave<T, false, true, false>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
-    else td_h_wave<T, false, false, false>(L, A, s, b, i0, j, k, Enew, Eold, tdw, C, z);
+    if (yz) td_h_wave<T, false, true, false>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
+    else td_h_wave<T, false, false, false>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
   }
 }
 
@@ -3406,6 +3488,10 @@ struct Dev {
   int *tile_tab[4] = {nullptr, nullptr, nullptr, nullptr};
   int *tl_off[4] = {nullptr, nullptr, nullptr, nullptr};
   int2 *tl_ent[4] = {nullptr, nullptr, nullptr, nullptr};
+  // the same for rows of waves (see build_rows), forward and adjoint runs
+  int2 *row_tab[2] = {nullptr, nullptr};
+  int *row_rec[2] = {nullptr, nullptr}, *row_src[2] = {nullptr, nullptr};
+  int rec_mask = 0;
   int ent_box[2][4] = {{0, -1, 0, -1}, {0, -1, 0, -1}};   // rows j and planes k of the E update's entries
   int ntg = 0;                  // forward injection targets (src_s .. src_coef)
   std::string list_key;
@@ -3465,6 +3551,10 @@ static void free_lists(Dev &d) {
   for (int m = 0; m < 4; ++m) {
     d.tile_tab[m] = d.tl_off[m] = nullptr;
     d.tl_ent[m] = nullptr;
+  }
+  for (int m = 0; m < 2; ++m) {
+    d.row_tab[m] = nullptr;
+    d.row_rec[m] = d.row_src[m] = nullptr;
   }
 }
 
@@ -3702,7 +3792,7 @@ static WS carve(const Plan &p, void *ws) {
 // x nodes, one plane per tile row (bz = k).  Fused: one x node per thread, kz planes per tile (bz = chunk).
 struct Tiling {
   int nbx, nby, nbz, nblocks, vx;
-  int bx, by, bz;   // threads of a tile along x and y, planes of a tile
+  int bx, by;   // threads of a tile along x and y
   size_t lds;   // dynamic LDS bytes per block (fused)
 };
 
@@ -3729,7 +3819,6 @@ static Tiling tiling(const Plan &p, bool h_update = false) {
   Tiling t;
   t.bx = p.bx;
   t.by = p.by;
-  t.bz = 1;
   if (wave_rows(p)) {
     // one wave a block: 64 nodes of a row (the nodes of the high walls are
     // skipped, see k_leap)
@@ -3773,21 +3862,84 @@ static std::string lists_key(const Plan &p) {
   return key;
 }
 
+template <typename V>
+static V *upload_list(Dev &d, const std::vector<V> &h) {
+  void *ptr = nullptr;
+  const size_t bytes = h.size() * sizeof(V);
+  HIP_CHECK(hipMalloc(&ptr, bytes ? bytes : 16));
+  d.list_bufs.push_back({ptr, bytes});
+  if (bytes) HIP_CHECK(hipMemcpy(ptr, h.data(), bytes, hipMemcpyHostToDevice));
+  return static_cast<V *>(ptr);
+}
+
+// Injections and receivers of rows of waves: a table of 64 lanes and six
+// components for every row with receiver nodes (an adjoint run injects at the
+// same nodes), and of every source's three E components for every row with a
+// source's edge (forward runs).  row_tab: the two tables of each row, or -1.
+// Also the rows and planes they span (ent_box).
+static void build_rows(Plan &p, Dev &d) {
+  const Tiling t = tiling(p);
+  const int nn = (int)p.rn_c.size();
+  const int64_t plane = (int64_t)p.NY * p.PX;
+  d.rec_mask = 0;
+  for (int mode = 0; mode < 2; ++mode) {
+    int *box = d.ent_box[mode];
+    box[0] = p.NY;
+    box[2] = p.NZ;
+    box[1] = box[3] = -1;
+    std::vector<int2> tab(t.nblocks, make_int2(-1, -1));
+    std::vector<int> rec, src;
+    // block and lane of a node
+    auto at = [&](int64_t idx, int &lane) -> int2 & {
+      const int k = (int)(idx / plane), j = (int)((idx % plane) / p.PX), i = (int)(idx % p.PX);
+      if (i >= p.nx || j >= p.ny || k >= p.nz) fail(FWD_ERR_INVALID_ARG, "entry outside the grid");
+      box[0] = std::min(box[0], j);
+      box[1] = std::max(box[1], j);
+      box[2] = std::min(box[2], k);
+      box[3] = std::max(box[3], k);
+      lane = i & 63;
+      const int bx = i >> 6;
+      return tab[p.order ? (j * t.nbx + bx) * t.nbz + k : (k * t.nby + j) * t.nbx + bx];
+    };
+    int lane;
+    for (int node = 0; node < nn; ++node) {
+      int2 &r = at(p.rn_idx[node], lane);
+      if (r.x < 0) {
+        r.x = (int)(rec.size() / 384);
+        rec.resize(rec.size() + 384, -1);
+      }
+      rec[((size_t)r.x * 6 + p.rn_c[node]) * 64 + lane] = node;
+      d.rec_mask |= 1 << p.rn_c[node];
+    }
+    if (mode == 0)
+      for (size_t q = 0; q < p.src_tg.size(); ++q) {
+        const auto &tg = p.src_tg[q];
+        if (tg.c >= 3) continue;              // into H, before the step or by the H update
+        int2 &r = at(tg.idx, lane);
+        const size_t one = (size_t)p.ns * 192;
+        if (r.y < 0) {
+          r.y = (int)(src.size() / one);
+          src.resize(src.size() + one, -1);
+        }
+        src[(((size_t)r.y * p.ns + tg.s) * 3 + tg.c) * 64 + lane] = (int)q;
+      }
+    d.row_tab[mode] = upload_list(d, tab);
+    d.row_rec[mode] = upload_list(d, rec);
+    d.row_src[mode] = upload_list(d, src);
+  }
+}
+
 static void build_lists(Plan &p, Dev &d) {
   const std::string key = lists_key(p);
   if (d.list_key == key) return;
   free_lists(d);
+  const bool rows = wave_rows(p);
+  if (rows) build_rows(p, d);
   const int nn = (int)p.rn_c.size(), nf = p.nf();
-  for (int mode = 0; mode < 4; ++mode) {
+  for (int mode = rows ? 2 : 0; mode < 4; ++mode) {
     const Tiling t = tiling(p, mode >= 2);   // modes 2 and 3 live on the H update's grid
     const bool own_h = p.sched != 1 && !one_launch(p);   // the H update adds magnetic sources
-    const int slots = t.bx * t.by * t.bz;
-    if (mode < 2) {
-      int *box = d.ent_box[mode];
-      box[0] = p.NY;
-      box[2] = p.NZ;
-      box[1] = box[3] = -1;
-    }
+    const int slots = t.bx * t.by;
     struct E {
       int b, slot;
       int2 v;
@@ -3797,13 +3949,6 @@ static void build_lists(Plan &p, Dev &d) {
       const int64_t plane = (int64_t)p.NY * p.PX;
       const int k = (int)(idx / plane), j = (int)((idx % plane) / p.PX), i = (int)(idx % p.PX);
       if (i > p.nx || j > p.ny || k > p.nz) fail(FWD_ERR_INVALID_ARG, "entry outside the grid");
-      if (mode < 2) {
-        int *box = d.ent_box[mode];
-        box[0] = std::min(box[0], j);
-        box[1] = std::max(box[1], j);
-        box[2] = std::min(box[2], k);
-        box[3] = std::max(box[3], k);
-      }
       int bxi, byi, bzi, slot, sub;
       if (p.sched == 1) {
         if (k >= p.nz) return;   // no E update on the top plane: never used
@@ -3814,9 +3959,9 @@ static void build_lists(Plan &p, Dev &d) {
       } else {
         const int tx = i / t.vx;
         sub = i % t.vx;
-        bzi = k / t.bz;
+        bzi = k;
         bxi = tx / t.bx;
-        slot = ((k % t.bz) * t.by + j % t.by) * t.bx + (tx % t.bx);
+        slot = (j % t.by) * t.bx + (tx % t.bx);
       }
       byi = j / t.by;
       const int b = p.order ? (byi * t.nbx + bxi) * t.nbz + bzi : (bzi * t.nby + byi) * t.nbx + bxi;
@@ -3876,16 +4021,9 @@ static void build_lists(Plan &p, Dev &d) {
       for (size_t g = e; g < f; ++g) ev.push_back(ents[g].v);
       e = f;
     }
-    auto up = [&](const void *h, size_t bytes) {
-      void *ptr = nullptr;
-      HIP_CHECK(hipMalloc(&ptr, bytes ? bytes : 16));
-      d.list_bufs.push_back({ptr, bytes});
-      if (bytes) HIP_CHECK(hipMemcpy(ptr, h, bytes, hipMemcpyHostToDevice));
-      return ptr;
-    };
-    d.tile_tab[mode] = static_cast<int *>(up(tab.data(), tab.size() * sizeof(int)));
-    d.tl_off[mode] = static_cast<int *>(up(off.data(), off.size() * sizeof(int)));
-    d.tl_ent[mode] = static_cast<int2 *>(up(ev.data(), ev.size() * sizeof(int2)));
+    d.tile_tab[mode] = upload_list(d, tab);
+    d.tl_off[mode] = upload_list(d, off);
+    d.tl_ent[mode] = upload_list(d, ev);
   }
   d.list_key = key;
 }
@@ -4117,7 +4255,11 @@ static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bo
   L.dnbx = A.dnbx;
   L.dnby = A.dnby;
   L.dnbz = A.dnbz;
-  L.tile_tab = A.tile_tab;
+  L.row_tab = d.row_tab[adj ? 1 : 0];
+  L.row_rec = d.row_rec[adj ? 1 : 0];
+  L.row_src = d.row_src[adj ? 1 : 0];
+  L.rec_mask = d.rec_mask;
+  L.adj = adj ? 1 : 0;
   const int *box = d.ent_box[adj ? 1 : 0];
   L.ej0 = box[0];
   L.ej1 = n < p.nt ? box[1] : -1;
@@ -4914,9 +5056,6 @@ static void adjoint_td_t(Plan &p, Dev &d, const WS &w, void *ws, char *scratch, 
   if (rows) {
     const Tiling t = tiling(p);
     set_grid(A, t.nbx, t.nby, t.nbz);
-    A.tile_tab = d.tile_tab[1];
-    A.tl_off = d.tl_off[1];
-    A.tl_ent = d.tl_ent[1];
     R = leap_args<T>(p, d, A, false, true, 0);
   }
   auto hsens = [&](int n) {

@@ -84,3 +84,22 @@ def test_graph_follows_rebuilt_entry_lists():
     E1 = p.forward().cpu().numpy()
     del hold
     assert np.abs(E0).max() > 0 and np.array_equal(E0, E1)
+
+
+@pytest.mark.parametrize("dtype,ns,nf", [("f64", 3, 5), ("f32", 1, 1), ("f64", 8, 3)])
+def test_entries_crowded_into_few_rows(dtype, ns, nf):
+    """Receivers that share rows, lanes and nodes with each other and with the
+    sources, every component, an odd number of frequencies: the rows' tables
+    against the lists of the two kernels."""
+    w = tiny(seed=47, n=(70, 9, 9), npml=2, ns=ns, moment_dirs=True, nr=9,
+             rec_comp=(0, 1, 2, 3, 4, 5)).replace(nt=33)
+    w = w.replace(freqs=np.linspace(0.2, 1.0, nf))
+    w.rec_pos[:] = w.src_pos[0]
+    w.rec_pos[:, 0] += np.linspace(-1.0, 1.0, 9) * 2.2 * np.diff(w.x).min()
+    w.rec_pos[-1] = w.rec_pos[0]
+    print(f"crowded entries, {dtype} ns {ns} nf {nf}", flush=True)
+    a = run(w, dtype, "f64")
+    b = run(w, dtype, "f64", vector=4, vector_h=4)
+    for x, y in zip(a, b):
+        assert np.isfinite(x).all() and np.abs(x).max() > 0
+        assert np.array_equal(x, y)
