@@ -3501,6 +3501,10 @@ struct Dev {
   double2 *eadj = nullptr;      // adjoint receiver transform when the caller passes none
   // graphs
   hipStream_t cap = nullptr;
+  // time-domain adjoint: 1/(sigma_e dV_e) [3][F], a table of the model built
+  // by the first call that needs it (6 of 22 ms of a gradient of 192 steps of
+  // 101x101x61 cells were spent building and sending it on each call)
+  const double *tdw = nullptr;
   hipGraphExec_t exec = nullptr;
   std::string exec_key;
   // sampled per-kernel timing
@@ -3614,6 +3618,7 @@ static void ensure_tables(Plan &p, hipStream_t stream) {
   HIP_CHECK(hipStreamSynchronize(stream));
   free_tables(d);
   d.vratio = nullptr;
+  d.tdw = nullptr;
   d.device = dev;
   if (!d.cap) HIP_CHECK(hipStreamCreateWithFlags(&d.cap, hipStreamNonBlocking));
   if (p.dtype == FWD_F64)
@@ -4968,8 +4973,7 @@ void dev_adjoint(Plan &p, void *ws, size_t ws_bytes, const void *vol, const doub
 // ---------------------------------------------------------------------------
 template <typename T>
 static void adjoint_td_t(Plan &p, Dev &d, const WS &w, void *ws, char *scratch, int L,
-                         const std::vector<double> &C, const std::vector<double> &Wt,
-                         double gscale, double *grad, int accumulate, hipStream_t st) {
+                         const std::vector<double> &C, double gscale, double *grad, int accumulate, hipStream_t st) {
   const int64_t F = p.field_elems();
   const int nt = p.nt, ns = p.ns, nn = (int)p.rn_c.size(), nf = p.nf();
   const int nseg = (nt + L - 1) / L;
@@ -4988,10 +4992,7 @@ static void adjoint_td_t(Plan &p, Dev &d, const WS &w, void *ws, char *scratch, 
   double *gedge = reinterpret_cast<double *>(b);
   b += a256((size_t)ns * 3 * F * 8);
   double2 *coef = reinterpret_cast<double2 *>(b);
-  b += a256((size_t)ns * nn * nf * 16);
-  double *tdw = reinterpret_cast<double *>(b);
   HIP_CHECK(hipMemcpyAsync(coef, C.data(), C.size() * sizeof(double), hipMemcpyHostToDevice, st));
-  HIP_CHECK(hipMemcpyAsync(tdw, Wt.data(), Wt.size() * sizeof(double), hipMemcpyHostToDevice, st));
   T *fields = static_cast<T *>(w.fields);
   const int64_t fbuf = (int64_t)ns * 6 * F, eslice = (int64_t)ns * 3 * F;
   const int cgrid = (int)std::min<int64_t>(((int64_t)ns * 3 * F + 255) / 256, 65536);
@@ -5079,19 +5080,19 @@ static void adjoint_td_t(Plan &p, Dev &d, const WS &w, void *ws, char *scratch, 
         const double2 *ze = n >= 1 ? d.zE + (int64_t)(n - 1) * nf : nullptr;
         hipLaunchKernelGGL((k_rows_td_e<T>), grid, row, 0, st, R, A, coef, zh);
         hipLaunchKernelGGL((k_rows_td_h<T>), grid, row, 0, st, R, A, eseg + (t + 1) * eslice,
-                           eseg + t * eslice, (const double *)tdw, coef, ze);
+                           eseg + t * eslice, d.tdw, coef, ze);
         continue;
       }
       if (p.fd_order == 4) {
         hipLaunchKernelGGL((k_td_e<T, 4>), grid, block, 0, st, A);
         hsens(n);
         hipLaunchKernelGGL((k_td_h<T, 4>), grid, block, 0, st, A, eseg + (t + 1) * eslice,
-                           eseg + t * eslice, (const double *)tdw);
+                           eseg + t * eslice, d.tdw);
       } else {
         hipLaunchKernelGGL((k_td_e<T, 2>), grid, block, 0, st, A);
         hsens(n);
         hipLaunchKernelGGL((k_td_h<T, 2>), grid, block, 0, st, A, eseg + (t + 1) * eslice,
-                           eseg + t * eslice, (const double *)tdw);
+                           eseg + t * eslice, d.tdw);
       }
       if (n >= 1) sens(n);
     }
@@ -5119,10 +5120,14 @@ void dev_adjoint_td(Plan &p, void *ws, size_t ws_bytes, void *scratch, size_t sc
   std::vector<double> rh(2 * nres);
   HIP_CHECK(hipMemcpyAsync(rh.data(), resid, rh.size() * sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_CHECK(hipStreamSynchronize(st));
-  std::vector<double> C, Wt;
+  std::vector<double> C;
   double scale = 1.0;
   td_coefficients(p, rh.data(), C, scale);
-  td_edge_weights(p, Wt);
+  if (!d.tdw) {
+    std::vector<double> W;
+    td_edge_weights(p, W);
+    d.tdw = upload(d, W);
+  }
   build_lists(p, d);
   d.kstat_n = 0;
   const double gscale = 1.0 / (p.src_scale * scale);
@@ -5131,13 +5136,13 @@ void dev_adjoint_td(Plan &p, void *ws, size_t ws_bytes, void *scratch, size_t sc
   HIP_CHECK(hipEventCreate(&e1));
   HIP_CHECK(hipEventRecord(e0, st));
   if (p.dtype == FWD_F64)
-    adjoint_td_t<double>(p, d, w, ws, static_cast<char *>(scratch), segment, C, Wt, gscale, grad,
+    adjoint_td_t<double>(p, d, w, ws, static_cast<char *>(scratch), segment, C, gscale, grad,
                          accumulate, st);
   else
-    adjoint_td_t<float>(p, d, w, ws, static_cast<char *>(scratch), segment, C, Wt, gscale, grad,
+    adjoint_td_t<float>(p, d, w, ws, static_cast<char *>(scratch), segment, C, gscale, grad,
                         accumulate, st);
   HIP_CHECK(hipEventRecord(e1, st));
-  HIP_CHECK(hipEventSynchronize(e1));   // C and Wt (host) stay alive until here
+  HIP_CHECK(hipEventSynchronize(e1));   // C (host) stays alive until here
   float ms = 0;
   HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
   (void)hipEventDestroy(e0);
