@@ -10,7 +10,9 @@
 //   one launch   k_leap, a wave per 64 nodes of a row, which recomputes the
 //                H it differences (order 2, one node per thread);
 //   two kernels  k_update_h then k_update_e, one thread per (i, j, k) node
-//                or per 16-byte vector of x nodes (order 4: their own forms);
+//                or per 16-byte vector of x nodes; order 4: k_rows_h4 then
+//                k_rows_e4, a wave per 64 nodes of a row, or their general
+//                forms k_update_h4 and k_update_e4;
 //   fused        k_step, one launch per step: a block owns a column tile and
 //                a chunk of z planes, stages each E plane (with a one-node
 //                halo) and the new H plane (with its low-side halo) in LDS,
@@ -145,24 +147,18 @@ struct StepArgs {
 // or z fastest, t = (by * nbx + bx) * nbz + bz (order 1: the blocks of
 // consecutive planes of a column tile run side by side, so the plane
 // neighbours a stencil reads are still in L2).  Returns the tile index.
-// XCD_RUNS (the one-wave blocks of k_leap): each XCD takes runs of 128
+// Rows of waves (row_of): each XCD takes runs of 128
 // consecutive b, dealt round-robin, and the blocks past the last whole round
 // stay where they are.  Rows of a run still share their neighbours in one L2,
 // and every XCD gets its part of the layers, whose rows cost twice as much:
 // with one contiguous range per XCD the XCDs of the outermost planes finish
 // last (101x101x61, 4 sources: 53.5 us a step against 47.5 with runs and 47.3
 // unmapped; 1 source: 17.5, 17.2 and 19.7; runs of 16 to 1024 within 4 %).
-enum { XCD_RUNS = 2, XCD_RUN_LOG2 = 7 };
+enum { XCD_RUN_LOG2 = 7 };
 template <typename Args>
 __device__ __forceinline__ int tile_of_b(const Args &A, uint32_t b, int &bx, int &by, int &bz,
                                          int &s) {
-  if (A.xcd == XCD_RUNS) {
-    constexpr uint32_t g = XCD_RUN_LOG2;
-    if (b < ((uint32_t)A.nblocks >> (3 + g)) << (3 + g)) {
-      const uint32_t x = b & 7u, local = b >> 3;
-      b = ((((local >> g) << 3) + x) << g) + (local & ((1u << g) - 1u));
-    }
-  } else if (A.xcd) {
+  if (A.xcd) {
     const uint32_t q = (uint32_t)A.nblocks >> 3, r = (uint32_t)A.nblocks & 7u;
     const uint32_t x = b & 7u, local = b >> 3;
     b = x * q + min(x, r) + local;
@@ -935,14 +931,19 @@ k_update_e_s(StepArgs<float> A) {
 // rows, layers and coefficients are scalar; every row is a 32-bit offset on
 // one buffer descriptor (a scalar add a row, 25 rows); the layers' branches
 // cost nothing off the layers; and three quarters of a large grid take the
-// form with none (141 scalar, 94 vector, 47 memory instructions a wave).
+// form with none (111 scalar, 92 vector, 56 memory instructions after the
+// block decode).  On 200x200x100 with 8 sources the texture addresser is busy
+// 86 % of the launch (43 % on 101x101x61, where issue bounds): waves of 62 own
+// nodes, whose end lanes carry the neighbours instead of one-lane loads, took
+// 15 % fewer instructions, but their rows leave the 128-byte lines (20.9 ->
+// 24.3 ms there; 12.25 -> 11.4 on 101x101x61 with 4 sources): not kept.
 // Rows of the high walls are not computed: H there stays zero (it
 // differences E edges on the wall), and E there is never updated.
 //
 // Measured a step, two kernels -> this (one MI355X): 101x101x61 FP32, 30.1 ->
-// 16.9 us; the same with 4 sources 77.2 -> 47.5 us; 200x200x100, 8 sources,
-// 943 -> 628 us (3.9 TB/s of the bytes it cannot do without); FP64
-// 128x128x96 113 -> 85 us.  Not kept: 2 nodes a lane
+// 16.9 us; the same with 4 sources 77.2 -> 46.4 us; 200x200x100, 8 sources,
+// 943 -> 610 us (4.0 TB/s of the bytes it cannot do without); FP64
+// 128x128x96 113 -> 82 us.  Not kept: 2 nodes a lane
 // (FP32; 20.5 us on the marine grid), a march in z with H of the plane below
 // carried (slower below 32 M node updates a step, 3 % faster above), blocks
 // of 4 rows (5 to 10 % slower than one-wave blocks), holding the layers'
@@ -1040,9 +1041,12 @@ struct LeapArgs {
   uint32_t sXb, sYb, sZb, oYb, oZb;  // psi slab strides and offsets in bytes
   int nx, ny, nz, npml, LA, NY;
   T dtmu;
-  int lean;
-  int nbx, nby, nbz, nblocks, xcd, order, ns;
-  FDiv dns, dnbx, dnby, dnbz;
+  int ns, order;
+  uint32_t runs;                     // blocks in whole rounds of runs (0: not remapped)
+  FDiv dns, d1, d2;                  // sources, tiles along the fastest and the next axis
+  // first and number of the wave starts i0, rows j and planes k that hold
+  // neither a layer nor a wall within the stencil's reach
+  uint32_t xs, xn, ys, yn, zs, zn;
   // injections and receivers by row (see build_rows): of each block's row its
   // receiver table and its source table, or -1
   const int2 *row_tab;
@@ -1050,8 +1054,45 @@ struct LeapArgs {
   const int *row_src;                // [tables][ns][3][64] first coefficient of its injection, or -1
   int rec_mask;                      // components that have receiver nodes at all (Ex .. Hz)
   int adj;                           // adjoint run: the E receiver nodes are the injections
-  int ej0, ej1, ek0, ek1;            // rows and planes that hold entries (empty: j1 < j0)
+  uint32_t ej, ejn, ek, ekn;         // first and number of the rows and planes they span
 };
+
+// Block -> (64-node tile of x, row, plane, source) and the row's index, for
+// rows of waves: as tile_of with runs of blocks an XCD, without branches.  The
+// scalar work before a wave's first load was 40 % of an interior wave's
+// instructions, so its limits and divisors come ready from the host (ms before
+// and after: 128x128x96 FP64 9.95 -> 9.65, 200x200x100 with 8 sources 20.9 ->
+// 20.4, 101x101x61 with 4 sources 12.25 -> 12.0, FP32 grids of some 10^4 cells
+// 2 to 12 % less).
+template <typename T>
+__device__ __forceinline__ int row_of(const LeapArgs<T> &L, int &bx, int &j, int &k, int &s) {
+  constexpr uint32_t g = XCD_RUN_LOG2;
+  uint32_t b = blockIdx.x;
+  const uint32_t local = b >> 3;
+  const uint32_t m = ((((local >> g) << 3) + (b & 7u)) << g) + (local & ((1u << g) - 1u));
+  b = b < L.runs ? m : b;
+  const uint32_t tile = fdiv(b, L.dns), t = fdiv(tile, L.d1), u = fdiv(t, L.d2);
+  s = (int)(b - tile * L.dns.d);
+  const int c0 = (int)(tile - t * L.d1.d), c1 = (int)(t - u * L.d2.d), c2 = (int)u;
+  bx = L.order ? c1 : c0;
+  j = L.order ? c2 : c1;
+  k = L.order ? c0 : c2;
+  return (int)tile;
+}
+// Which variant a row takes: a layer or a wall (within the nodes that the
+// differences reach) in x, and in y or z
+template <typename T>
+__device__ __forceinline__ void row_kind(const LeapArgs<T> &L, int i0, int j, int k, bool &xl, bool &yz) {
+  xl = (uint32_t)i0 - L.xs >= L.xn;
+  yz = ((uint32_t)j - L.ys >= L.yn) | ((uint32_t)k - L.zs >= L.zn);
+}
+// The tables of a row, if any (rows outside the box of the entries do not ask)
+template <typename T>
+__device__ __forceinline__ int2 row_tables(const LeapArgs<T> &L, int b, int j, int k) {
+  int2 row = make_int2(-1, -1);
+  if (((uint32_t)j - L.ej < L.ejn) & ((uint32_t)k - L.ek < L.ekn)) row = L.row_tab[b];
+  return row;
+}
 
 // The lane's receiver nodes and injections.  A lane has at most one of each a
 // component, so they come as rows of lanes: the loads of all components, then
@@ -1065,19 +1106,19 @@ struct RowEnt {
   int node[6], src[3];
 };
 template <typename T>
-__device__ __forceinline__ RowEnt row_entries(const LeapArgs<T> &L, const StepArgs<T> &A, int2 tt, int s,
+__device__ __forceinline__ RowEnt row_entries(const LeapArgs<T> &L, const StepArgs<T> &A, int2 row, int s,
                                               int tid) {
   RowEnt e;
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
     e.node[c] = -1;
-    if (tt.x >= 0 && (L.rec_mask >> c & 1)) e.node[c] = L.row_rec[(tt.x * 6 + c) * 64 + tid];
+    if (row.x >= 0 && (L.rec_mask >> c & 1)) e.node[c] = L.row_rec[(row.x * 6 + c) * 64 + tid];
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     e.src[c] = -1;
     if (L.adj) e.src[c] = e.node[c] >= 0 ? (s * A.nn + e.node[c]) * A.nrow : -1;
-    else if (tt.y >= 0) e.src[c] = L.row_src[((tt.y * L.ns + s) * 3 + c) * 64 + tid];
+    else if (row.y >= 0) e.src[c] = L.row_src[((row.y * L.ns + s) * 3 + c) * 64 + tid];
   }
   return e;
 }
@@ -1124,20 +1165,10 @@ __device__ __forceinline__ void record_row(const StepArgs<T> &A, const RowEnt &e
   }
 }
 
-// The tables of a row with entries.  The kernel has read them to choose the
-// variant; FP32 reads them again, because kept over the choice they took 25
-// registers more (140: three waves a SIMD for four, 101x101x61 with 4 sources
-// 13.5 ms against 12.3), while FP64 stays at two waves either way.
-template <typename T, bool ENT>
-__device__ __forceinline__ int2 own_row(const LeapArgs<T> &L, int b, int2 row) {
-  if constexpr (ENT && sizeof(T) == 4) return L.row_tab[b];
-  return row;
-}
-
 // XL: nodes of the wave may lie in an x layer or at an x wall; YZ: the row
 // may lie in a y or z layer or at a wall; ENT: it holds entries (row: its tables).
 template <typename T, bool HIST, bool NT, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int2 row,
+__device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int2 row,
                                           int i0, int j, int k) {
   // coefficients of the rows j, j - 1, k, k - 1 and of i0 - 1: read before
   // the marker below, so that they are scalar loads
@@ -1145,7 +1176,6 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   const int jm = j_lo ? j - 1 : j, km = k_lo ? k - 1 : k;
   const AxRow<T> yj = L.axr[L.LA + j], ym = L.axr[L.LA + jm], zk = L.axr[2 * L.LA + k],
                  zm = L.axr[2 * L.LA + km], xl = L.axr[left ? i0 - 1 : 0];
-  const int2 tt = own_row<T, ENT>(L, b, row);
   const int n = ENT ? L.step[0] + 1 : 0;
   // each variant starts with its own marker: loads common to the variants
   // are not hoisted above the branches (that kept the registers of all of
@@ -1156,7 +1186,7 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   const uint32_t sz = sizeof(T);
   const bool i_lo = !XL || i >= 1;
   RowEnt ent;
-  if constexpr (ENT) ent = row_entries(L, A, tt, s, tid);
+  if constexpr (ENT) ent = row_entries(L, A, row, s, tid);
   // rows below a wall are replaced by the node's own: their values reach no
   // stored result
   const uint32_t dj = L.PXb, ej = j_lo ? 0u - L.PXb : 0u;
@@ -1290,7 +1320,10 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
     }
   }
   double inj[3];
-  if constexpr (ENT) inject_row(A, ent, n, inj);
+  // FP64: the injections' loads beside the stencil's.  FP32: after the update,
+  // where they need no registers beside the stencil's (141 otherwise, three
+  // waves a SIMD for four: 13.0 ms against 12.0 with 4 sources on 101x101x61).
+  if constexpr (ENT && sizeof(T) == 8) inject_row(A, ent, n, inj);
   // ---- H^{n+1/2} at the node and, recomputed, at j - 1, k - 1 and i - 1 ----
   const T mc = -L.dtmu;
   const T hj = yj.ih, hjm = ym.ih, hk = zk.ih, hkm = zm.ih;
@@ -1321,6 +1354,7 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   T e1y = curl_update<YZ, XL>(ey0, cy, Hx, Hxk, zk.ihd, pzn, ey_z, zn, Hz, Hzi, ihd, pxn, ey_x, xn);
   T e1z = curl_update<XL, YZ>(ez0, cz, Hy, Hyi, ihd, pxn, ez_x, xn, Hx, Hxj, yj.ihd, pyn, ez_y, yn);
   if constexpr (ENT) {
+    if constexpr (sizeof(T) == 4) inject_row(A, ent, n, inj);
     e1x -= (T)((double)cx * inj[0]);
     e1y -= (T)((double)cy * inj[1]);
     e1z -= (T)((double)cz * inj[2]);
@@ -1387,24 +1421,23 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
 template <typename T, bool HIST, bool NT>
 __global__ void __launch_bounds__(64) k_leap(LeapArgs<T> L, StepArgs<T> A) {
   int bx, j, k, s;
-  const int b = tile_of(L, bx, j, k, s);
+  const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
-  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = L.step[0] + 1;
   if (i0 + (int)threadIdx.x >= L.nx) return;
-  const int np = L.npml;
-  const bool xl = !L.lean || i0 <= np || i0 + 64 > L.nx - np;
-  const bool yz = !L.lean || j <= np || j >= L.ny - np || k <= np || k >= L.nz - np;
-  int2 row = make_int2(-1, -1);   // rows outside the box of the entries do not ask
-  if (j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1) row = L.row_tab[b];
+  bool xl, yz;
+  row_kind(L, i0, j, k, xl, yz);
+  const int2 row = row_tables(L, b, j, k);
   if (max(row.x, row.y) >= 0)
-    leap_wave<T, HIST, NT, true, true, true>(L, A, s, b, row, i0, j, k);
+    leap_wave<T, HIST, NT, true, true, true>(L, A, s, row, i0, j, k);
   else if (xl) {
-    if (yz) leap_wave<T, HIST, NT, true, true, false>(L, A, s, b, row, i0, j, k);
-    else leap_wave<T, HIST, NT, true, false, false>(L, A, s, b, row, i0, j, k);
+    if (yz) leap_wave<T, HIST, NT, true, true, false>(L, A, s, row, i0, j, k);
+    else leap_wave<T, HIST, NT, true, false, false>(L, A, s, row, i0, j, k);
   } else {
-    if (yz) leap_wave<T, HIST, NT, false, true, false>(L, A, s, b, row, i0, j, k);
-    else leap_wave<T, HIST, NT, false, false, false>(L, A, s, b, row, i0, j, k);
+    if (yz) leap_wave<T, HIST, NT, false, true, false>(L, A, s, row, i0, j, k);
+    else leap_wave<T, HIST, NT, false, false, false>(L, A, s, row, i0, j, k);
   }
+  // last: a store before them would turn the uniform loads into vector ones
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = L.step[0] + 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -1740,15 +1773,14 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
 }
 
 template <typename T, bool HIST, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int2 row, int i0,
+__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int2 row, int i0,
                                         int j, int k) {
   const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];
-  const int2 tt = own_row<T, ENT>(L, b, row);
   const int n = ENT ? L.step[0] + 1 : 0;
   asm volatile("; e4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));
   const int tid = threadIdx.x, i = i0 + tid;
   RowEnt ent;
-  if constexpr (ENT) ent = row_entries(L, A, tt, s, tid);
+  if constexpr (ENT) ent = row_entries(L, A, row, s, tid);
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T);
   const uint32_t x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
@@ -1883,19 +1915,10 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   }
 }
 
-// Which variant a row takes: a layer or a wall (within the two nodes that the
-// differences reach) in x, and in y or z
-template <typename T>
-__device__ __forceinline__ void row_kind(const LeapArgs<T> &L, int i0, int j, int k, bool &xl, bool &yz) {
-  const int np = max(L.npml, 2);
-  xl = !L.lean || i0 <= np || i0 + 64 > L.nx - np;
-  yz = !L.lean || j <= np || j >= L.ny - np || k <= np || k >= L.nz - np;
-}
-
 template <typename T, bool INJ>
 __global__ void __launch_bounds__(64) k_rows_h4(LeapArgs<T> L, StepArgs<T> A) {
   int bx, j, k, s;
-  const int b = tile_of(L, bx, j, k, s);
+  const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
@@ -1914,23 +1937,22 @@ __global__ void __launch_bounds__(64) k_rows_h4(LeapArgs<T> L, StepArgs<T> A) {
 template <typename T, bool HIST>
 __global__ void __launch_bounds__(64) k_rows_e4(LeapArgs<T> L, StepArgs<T> A) {
   int bx, j, k, s;
-  const int b = tile_of(L, bx, j, k, s);
+  const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
-  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = L.step[0] + 1;
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
-  int2 row = make_int2(-1, -1);
-  if (j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1) row = L.row_tab[b];
+  const int2 row = row_tables(L, b, j, k);
   if (max(row.x, row.y) >= 0)
-    e4_wave<T, HIST, true, true, true>(L, A, s, b, row, i0, j, k);
+    e4_wave<T, HIST, true, true, true>(L, A, s, row, i0, j, k);
   else if (xl) {
-    if (yz) e4_wave<T, HIST, true, true, false>(L, A, s, b, row, i0, j, k);
-    else e4_wave<T, HIST, true, false, false>(L, A, s, b, row, i0, j, k);
+    if (yz) e4_wave<T, HIST, true, true, false>(L, A, s, row, i0, j, k);
+    else e4_wave<T, HIST, true, false, false>(L, A, s, row, i0, j, k);
   } else {
-    if (yz) e4_wave<T, HIST, false, true, false>(L, A, s, b, row, i0, j, k);
-    else e4_wave<T, HIST, false, false, false>(L, A, s, b, row, i0, j, k);
+    if (yz) e4_wave<T, HIST, false, true, false>(L, A, s, row, i0, j, k);
+    else e4_wave<T, HIST, false, false, false>(L, A, s, row, i0, j, k);
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = L.step[0] + 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -2748,7 +2770,7 @@ __global__ void __launch_bounds__(256) k_td_h(StepArgs<T> A, const T *Enew, cons
 // The reverse step of order 2 as rows of waves (where k_leap runs the forward
 // steps): one wave a block, 64 nodes of one row; rows, coefficients, layer
 // tests and offsets are scalar, and the x neighbour's term comes from the lane
-// beside (the wave's edge lane computes it).  The entry lists of the adjoint
+// beside (the wave's edge lane computes it).  The receiver tables of the adjoint
 // runs add the receivers' sensitivities to the owner's new multiplier, so the
 // two launches are the whole reverse step.  XL, YZ, ENT: as k_leap.
 // The same operations in the same order as the general kernels.
@@ -2793,15 +2815,14 @@ __device__ __forceinline__ void td_sens_row(const StepArgs<T> &A, const RowEnt &
 }
 
 template <typename T, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int2 row, int i0,
+__device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int2 row, int i0,
                                           int j, int k, const double2 *C, const double2 *z) {
   const AxRow<T> yj = L.axr[L.LA + j], yp = L.axr[L.LA + j + 1], zk = L.axr[2 * L.LA + k],
                  zp = L.axr[2 * L.LA + k + 1], xr = L.axr[min(i0 + 64, L.nx)];
-  const int2 tt = own_row<T, ENT>(L, b, row);
   asm volatile("; tde %0" ::"n"(XL * 4 + YZ * 2 + ENT));   // see leap_wave
   const int tid = threadIdx.x, i = i0 + tid;
   RowEnt ent;
-  if constexpr (ENT) ent = row_entries(L, A, tt, s, tid);
+  if constexpr (ENT) ent = row_entries(L, A, row, s, tid);
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T), x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
   const uint32_t q = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0, qj = q + L.PXb, qk = q + L.PLb;
@@ -2939,18 +2960,17 @@ __device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T
 }
 
 template <typename T, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int2 row, int i0,
+__device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int2 row, int i0,
                                           int j, int k, const T *Enew, const T *Eold, const double *tdw,
                                           const double2 *C, const double2 *z) {
   const bool j_lo = !YZ || j >= 1, k_lo = !YZ || k >= 1, left = !XL || i0 > 0;
   const int jm = j_lo ? j - 1 : j, km = k_lo ? k - 1 : k;
   const AxRow<T> yj = L.axr[L.LA + j], ym = L.axr[L.LA + jm], zk = L.axr[2 * L.LA + k],
                  zm = L.axr[2 * L.LA + km], xl = L.axr[left ? i0 - 1 : 0];
-  const int2 tt = own_row<T, ENT>(L, b, row);
   asm volatile("; tdh %0" ::"n"(XL * 4 + YZ * 2 + ENT));   // see leap_wave
   const int tid = threadIdx.x, i = i0 + tid;
   RowEnt ent;
-  if constexpr (ENT) ent = row_entries(L, A, tt, s, tid);
+  if constexpr (ENT) ent = row_entries(L, A, row, s, tid);
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T), x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
   const uint32_t q = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0;
@@ -3103,22 +3123,22 @@ template <typename T>
 __global__ void __launch_bounds__(64) k_rows_td_e(LeapArgs<T> L, StepArgs<T> A, const double2 *C,
                                                   const double2 *z) {
   int bx, j, k, s;
-  const int b = tile_of(L, bx, j, k, s);
+  const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
   // z: null where no magnetic receiver is recorded
   int2 row = make_int2(-1, -1);
-  if (z && j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1) row = L.row_tab[b];
+  if (z) row = row_tables(L, b, j, k);
   if (max(row.x, row.y) >= 0)
-    td_e_wave<T, true, true, true>(L, A, s, b, row, i0, j, k, C, z);
+    td_e_wave<T, true, true, true>(L, A, s, row, i0, j, k, C, z);
   else if (xl) {
-    if (yz) td_e_wave<T, true, true, false>(L, A, s, b, row, i0, j, k, C, z);
-    else td_e_wave<T, true, false, false>(L, A, s, b, row, i0, j, k, C, z);
+    if (yz) td_e_wave<T, true, true, false>(L, A, s, row, i0, j, k, C, z);
+    else td_e_wave<T, true, false, false>(L, A, s, row, i0, j, k, C, z);
   } else {
-    if (yz) td_e_wave<T, false, true, false>(L, A, s, b, row, i0, j, k, C, z);
-    else td_e_wave<T, false, false, false>(L, A, s, b, row, i0, j, k, C, z);
+    if (yz) td_e_wave<T, false, true, false>(L, A, s, row, i0, j, k, C, z);
+    else td_e_wave<T, false, false, false>(L, A, s, row, i0, j, k, C, z);
   }
 }
 
@@ -3126,22 +3146,22 @@ template <typename T>
 __global__ void __launch_bounds__(64) k_rows_td_h(LeapArgs<T> L, StepArgs<T> A, const T *Enew, const T *Eold,
                                                   const double *tdw, const double2 *C, const double2 *z) {
   int bx, j, k, s;
-  const int b = tile_of(L, bx, j, k, s);
+  const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
   // z: null at the first step (no sample before it)
   int2 row = make_int2(-1, -1);
-  if (z && j >= L.ej0 && j <= L.ej1 && k >= L.ek0 && k <= L.ek1) row = L.row_tab[b];
+  if (z) row = row_tables(L, b, j, k);
   if (max(row.x, row.y) >= 0)
-    td_h_wave<T, true, true, true>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
+    td_h_wave<T, true, true, true>(L, A, s, row, i0, j, k, Enew, Eold, tdw, C, z);
   else if (xl) {
-    if (yz) td_h_wave<T, true, true, false>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
-    else td_h_wave<T, true, false, false>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
+    if (yz) td_h_wave<T, true, true, false>(L, A, s, row, i0, j, k, Enew, Eold, tdw, C, z);
+    else td_h_wave<T, true, false, false>(L, A, s, row, i0, j, k, Enew, Eold, tdw, C, z);
   } else {
-    if (yz) td_h_wave<T, false, true, false>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
-    else td_h_wave<T, false, false, false>(L, A, s, b, row, i0, j, k, Enew, Eold, tdw, C, z);
+    if (yz) td_h_wave<T, false, true, false>(L, A, s, row, i0, j, k, Enew, Eold, tdw, C, z);
+    else td_h_wave<T, false, false, false>(L, A, s, row, i0, j, k, Enew, Eold, tdw, C, z);
   }
 }
 
@@ -4248,28 +4268,32 @@ static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bo
   L.LA = A.LA;
   L.NY = A.NY;
   L.dtmu = A.dtmu;
-  L.lean = A.lean;
-  L.nbx = A.nbx;
-  L.nby = A.nby;
-  L.nbz = A.nbz;
-  L.nblocks = A.nblocks;
-  L.xcd = A.xcd ? XCD_RUNS : 0;
   L.order = A.order;
   L.ns = A.ns;
+  L.runs = A.xcd ? (uint32_t)A.nblocks >> (3 + XCD_RUN_LOG2) << (3 + XCD_RUN_LOG2) : 0;
   L.dns = A.dns;
-  L.dnbx = A.dnbx;
-  L.dnby = A.dnby;
-  L.dnbz = A.dnbz;
+  L.d1 = A.order ? A.dnbz : A.dnbx;
+  L.d2 = A.order ? A.dnbx : A.dnby;
+  // differences reach one node past the layer's edge rows, and two past a
+  // wall at order 4
+  const int np = p.fd_order == 4 ? std::max(A.npml, 2) : A.npml;
+  auto window = [&](int n, int width, uint32_t &first, uint32_t &count) {
+    first = (uint32_t)np + 1;
+    count = A.lean ? (uint32_t)std::max(0, n - 2 * np - width) : 0;
+  };
+  window(A.nx, 64, L.xs, L.xn);
+  window(A.ny, 1, L.ys, L.yn);
+  window(A.nz, 1, L.zs, L.zn);
   L.row_tab = d.row_tab[adj ? 1 : 0];
   L.row_rec = d.row_rec[adj ? 1 : 0];
   L.row_src = d.row_src[adj ? 1 : 0];
   L.rec_mask = d.rec_mask;
   L.adj = adj ? 1 : 0;
   const int *box = d.ent_box[adj ? 1 : 0];
-  L.ej0 = box[0];
-  L.ej1 = n < p.nt ? box[1] : -1;
-  L.ek0 = box[2];
-  L.ek1 = box[3];
+  L.ej = (uint32_t)box[0];
+  L.ejn = n < p.nt ? (uint32_t)std::max(0, box[1] - box[0] + 1) : 0;
+  L.ek = (uint32_t)box[2];
+  L.ekn = (uint32_t)std::max(0, box[3] - box[2] + 1);
   const int D = adj ? 1 : p.dec, m = n + 1, r = m / D & (p.kb - 1);
   const bool hist = vol && n < p.nt && m % D == 0 && r != 0;
   if (hist) L.hist = A.hist + (int64_t)(r - 1) * 3 * A.F;
