@@ -3529,7 +3529,7 @@ struct Dev {
   std::string exec_key;
   // sampled per-kernel timing
   std::vector<hipEvent_t> ev;                  // six per sampled step
-  std::vector<uint8_t> kstat_closed;           // the sampled step closed a transform block
+  std::vector<uint8_t> kstat_closed;           // bit 0: the sampled step closed a transform block; 1: one launch a step
   double kstat_ms[3] = {0, 0, 0};
   int kstat_n = 0, kstat_ntr = 0;
   int sample_every = 0;
@@ -4585,7 +4585,7 @@ static void run_steps_t(Plan &p, Dev &d, const WS &w, void *vol, bool adj, int n
       enqueue_step<T>(p, d, w, vol, adj, st, ev, r, p.host_step, &closed);
       if (timed) {
         d.kstat_closed.resize((size_t)d.kstat_n + 1);
-        d.kstat_closed[d.kstat_n] = closed ? 1 : 0;
+        d.kstat_closed[d.kstat_n] = (closed ? 1 : 0) | (one_launch(p) || p.sched == 1 ? 2 : 0);
         d.kstat_n++;
       }
       p.host_step++;
@@ -4659,12 +4659,13 @@ static void collect_kernel_stats(Dev &d) {
   for (int s = 0; s < d.kstat_n; ++s) {
     hipEvent_t *ev = &d.ev[(size_t)s * 6];
     for (int k = 0; k < 3; ++k) {
-      if (k == 2 && !d.kstat_closed[s]) continue;
+      if (k == 2 && !(d.kstat_closed[s] & 1)) continue;
+      if (k == 0 && (d.kstat_closed[s] & 2)) continue;   // one launch: no H update of its own
       float ms = 0;
       HIP_CHECK(hipEventElapsedTime(&ms, ev[2 * k], ev[2 * k + 1]));
       tot[k] += ms;
     }
-    ntr += d.kstat_closed[s];
+    ntr += d.kstat_closed[s] & 1;
   }
   for (int k = 0; k < 2; ++k) d.kstat_ms[k] = d.kstat_n ? tot[k] / d.kstat_n : 0.0;
   d.kstat_ms[2] = ntr ? tot[2] / ntr : 0.0;

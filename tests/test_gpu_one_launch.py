@@ -103,3 +103,16 @@ def test_entries_crowded_into_few_rows(dtype, ns, nf):
     for x, y in zip(a, b):
         assert np.isfinite(x).all() and np.abs(x).max() > 0
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("order,xcd,ns", [(0, 1, 2), (1, 1, 2), (1, 0, 3), (0, 1, 1)])
+def test_decode_over_whole_rounds_of_runs(order, xcd, ns):
+    """More than 1024 blocks: runs of 128 blocks an XCD, the blocks past the
+    last whole round, both tile orders (the volume holds every row)."""
+    w = tiny(seed=48, n=(66, 31, 21), npml=2, ns=ns, moment_dirs=True, nr=4).replace(nt=19)
+    print(f"decode over rounds of runs, tile order {order} xcd {xcd} ns {ns}", flush=True)
+    a = run(w, "f32", "f64", tile_order=order, xcd_remap=xcd)
+    b = run(w, "f32", "f64", vector=4, vector_h=4)
+    assert np.abs(a[1]).max() > 0        # the volume; 19 steps may not reach a receiver
+    for x, y in zip(a, b):
+        assert np.isfinite(x).all() and np.array_equal(x, y)
