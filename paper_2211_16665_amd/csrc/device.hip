@@ -1047,11 +1047,11 @@ struct LeapArgs {
   // first and number of the wave starts i0, rows j and planes k that hold
   // neither a layer nor a wall within the stencil's reach
   uint32_t xs, xn, ys, yn, zs, zn;
-  // injections and receivers by row (see build_rows): of each block's row its
-  // receiver table and its source table, or -1
-  const int2 *row_tab;
+  // injections and receivers by row (see build_rows): of each row its receiver
+  // table, of each row and source its source table, or -1 (adjoint runs: null)
+  const int *row_tab, *src_tab;
   const int *row_rec;                // [tables][6][64] receiver node of the lane's component, or -1
-  const int *row_src;                // [tables][ns][3][64] first coefficient of its injection, or -1
+  const int *row_src;                // [tables][3][64] first coefficient of its injection, or -1
   int rec_mask;                      // components that have receiver nodes at all (Ex .. Hz)
   int adj;                           // adjoint run: the E receiver nodes are the injections
   uint32_t ej, ejn, ek, ekn;         // first and number of the rows and planes they span
@@ -1088,9 +1088,12 @@ __device__ __forceinline__ void row_kind(const LeapArgs<T> &L, int i0, int j, in
 }
 // The tables of a row, if any (rows outside the box of the entries do not ask)
 template <typename T>
-__device__ __forceinline__ int2 row_tables(const LeapArgs<T> &L, int b, int j, int k) {
+__device__ __forceinline__ int2 row_tables(const LeapArgs<T> &L, int b, int j, int k, int s) {
   int2 row = make_int2(-1, -1);
-  if (((uint32_t)j - L.ej < L.ejn) & ((uint32_t)k - L.ek < L.ekn)) row = L.row_tab[b];
+  if (((uint32_t)j - L.ej < L.ejn) & ((uint32_t)k - L.ek < L.ekn)) {
+    row.x = L.row_tab[b];
+    if (L.src_tab) row.y = L.src_tab[b * L.ns + s];
+  }
   return row;
 }
 
@@ -1118,7 +1121,7 @@ __device__ __forceinline__ RowEnt row_entries(const LeapArgs<T> &L, const StepAr
   for (int c = 0; c < 3; ++c) {
     e.src[c] = -1;
     if (L.adj) e.src[c] = e.node[c] >= 0 ? (s * A.nn + e.node[c]) * A.nrow : -1;
-    else if (row.y >= 0) e.src[c] = L.row_src[((row.y * L.ns + s) * 3 + c) * 64 + tid];
+    else if (row.y >= 0) e.src[c] = L.row_src[(row.y * 3 + c) * 64 + tid];
   }
   return e;
 }
@@ -1426,7 +1429,7 @@ __global__ void __launch_bounds__(64) k_leap(LeapArgs<T> L, StepArgs<T> A) {
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
-  const int2 row = row_tables(L, b, j, k);
+  const int2 row = row_tables(L, b, j, k, s);
   if (max(row.x, row.y) >= 0)
     leap_wave<T, HIST, NT, true, true, true>(L, A, s, row, i0, j, k);
   else if (xl) {
@@ -1942,7 +1945,7 @@ __global__ void __launch_bounds__(64) k_rows_e4(LeapArgs<T> L, StepArgs<T> A) {
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
-  const int2 row = row_tables(L, b, j, k);
+  const int2 row = row_tables(L, b, j, k, s);
   if (max(row.x, row.y) >= 0)
     e4_wave<T, HIST, true, true, true>(L, A, s, row, i0, j, k);
   else if (xl) {
@@ -3130,7 +3133,7 @@ __global__ void __launch_bounds__(64) k_rows_td_e(LeapArgs<T> L, StepArgs<T> A, 
   row_kind(L, i0, j, k, xl, yz);
   // z: null where no magnetic receiver is recorded
   int2 row = make_int2(-1, -1);
-  if (z) row = row_tables(L, b, j, k);
+  if (z) row = row_tables(L, b, j, k, s);
   if (max(row.x, row.y) >= 0)
     td_e_wave<T, true, true, true>(L, A, s, row, i0, j, k, C, z);
   else if (xl) {
@@ -3153,7 +3156,7 @@ __global__ void __launch_bounds__(64) k_rows_td_h(LeapArgs<T> L, StepArgs<T> A, 
   row_kind(L, i0, j, k, xl, yz);
   // z: null at the first step (no sample before it)
   int2 row = make_int2(-1, -1);
-  if (z) row = row_tables(L, b, j, k);
+  if (z) row = row_tables(L, b, j, k, s);
   if (max(row.x, row.y) >= 0)
     td_h_wave<T, true, true, true>(L, A, s, row, i0, j, k, Enew, Eold, tdw, C, z);
   else if (xl) {
@@ -3509,8 +3512,7 @@ struct Dev {
   int *tl_off[4] = {nullptr, nullptr, nullptr, nullptr};
   int2 *tl_ent[4] = {nullptr, nullptr, nullptr, nullptr};
   // the same for rows of waves (see build_rows), forward and adjoint runs
-  int2 *row_tab[2] = {nullptr, nullptr};
-  int *row_rec[2] = {nullptr, nullptr}, *row_src[2] = {nullptr, nullptr};
+  int *row_tab = nullptr, *src_tab = nullptr, *row_rec = nullptr, *row_src = nullptr;
   int rec_mask = 0;
   int ent_box[2][4] = {{0, -1, 0, -1}, {0, -1, 0, -1}};   // rows j and planes k of the E update's entries
   int ntg = 0;                  // forward injection targets (src_s .. src_coef)
@@ -3576,10 +3578,7 @@ static void free_lists(Dev &d) {
     d.tile_tab[m] = d.tl_off[m] = nullptr;
     d.tl_ent[m] = nullptr;
   }
-  for (int m = 0; m < 2; ++m) {
-    d.row_tab[m] = nullptr;
-    d.row_rec[m] = d.row_src[m] = nullptr;
-  }
+  d.row_tab = d.src_tab = d.row_rec = d.row_src = nullptr;
 }
 
 static void free_tables(Dev &d) {
@@ -3899,59 +3898,61 @@ static V *upload_list(Dev &d, const std::vector<V> &h) {
 
 // Injections and receivers of rows of waves: a table of 64 lanes and six
 // components for every row with receiver nodes (an adjoint run injects at the
-// same nodes), and of every source's three E components for every row with a
-// source's edge (forward runs).  row_tab: the two tables of each row, or -1.
-// Also the rows and planes they span (ent_box).
+// same nodes), and one of the three E components for every row and source
+// with an edge of that source (forward runs; a table a row for all sources
+// would grow with their square).  Also the rows and planes that the entries
+// of either run span (ent_box).
 static void build_rows(Plan &p, Dev &d) {
   const Tiling t = tiling(p);
   const int nn = (int)p.rn_c.size();
   const int64_t plane = (int64_t)p.NY * p.PX;
-  d.rec_mask = 0;
-  for (int mode = 0; mode < 2; ++mode) {
-    int *box = d.ent_box[mode];
+  std::vector<int> tab(t.nblocks, -1), stab((size_t)t.nblocks * p.ns, -1), rec, src;
+  for (int m = 0; m < 2; ++m) {
+    int *box = d.ent_box[m];
     box[0] = p.NY;
     box[2] = p.NZ;
     box[1] = box[3] = -1;
-    std::vector<int2> tab(t.nblocks, make_int2(-1, -1));
-    std::vector<int> rec, src;
-    // block and lane of a node
-    auto at = [&](int64_t idx, int &lane) -> int2 & {
-      const int k = (int)(idx / plane), j = (int)((idx % plane) / p.PX), i = (int)(idx % p.PX);
-      if (i >= p.nx || j >= p.ny || k >= p.nz) fail(FWD_ERR_INVALID_ARG, "entry outside the grid");
+  }
+  // row (its tile) and lane of a node; run: the runs whose entry it is from
+  auto at = [&](int64_t idx, int run, int &lane) {
+    const int k = (int)(idx / plane), j = (int)((idx % plane) / p.PX), i = (int)(idx % p.PX);
+    if (i >= p.nx || j >= p.ny || k >= p.nz) fail(FWD_ERR_INVALID_ARG, "entry outside the grid");
+    for (int m = 0; m <= run; ++m) {
+      int *box = d.ent_box[m];
       box[0] = std::min(box[0], j);
       box[1] = std::max(box[1], j);
       box[2] = std::min(box[2], k);
       box[3] = std::max(box[3], k);
-      lane = i & 63;
-      const int bx = i >> 6;
-      return tab[p.order ? (j * t.nbx + bx) * t.nbz + k : (k * t.nby + j) * t.nbx + bx];
-    };
-    int lane;
-    for (int node = 0; node < nn; ++node) {
-      int2 &r = at(p.rn_idx[node], lane);
-      if (r.x < 0) {
-        r.x = (int)(rec.size() / 384);
-        rec.resize(rec.size() + 384, -1);
-      }
-      rec[((size_t)r.x * 6 + p.rn_c[node]) * 64 + lane] = node;
-      d.rec_mask |= 1 << p.rn_c[node];
     }
-    if (mode == 0)
-      for (size_t q = 0; q < p.src_tg.size(); ++q) {
-        const auto &tg = p.src_tg[q];
-        if (tg.c >= 3) continue;              // into H, before the step or by the H update
-        int2 &r = at(tg.idx, lane);
-        const size_t one = (size_t)p.ns * 192;
-        if (r.y < 0) {
-          r.y = (int)(src.size() / one);
-          src.resize(src.size() + one, -1);
-        }
-        src[(((size_t)r.y * p.ns + tg.s) * 3 + tg.c) * 64 + lane] = (int)q;
-      }
-    d.row_tab[mode] = upload_list(d, tab);
-    d.row_rec[mode] = upload_list(d, rec);
-    d.row_src[mode] = upload_list(d, src);
+    lane = i & 63;
+    const int bx = i >> 6;
+    return p.order ? (j * t.nbx + bx) * t.nbz + k : (k * t.nby + j) * t.nbx + bx;
+  };
+  int lane = 0;
+  d.rec_mask = 0;
+  for (int node = 0; node < nn; ++node) {
+    int &r = tab[at(p.rn_idx[node], 1, lane)];
+    if (r < 0) {
+      r = (int)(rec.size() / 384);
+      rec.resize(rec.size() + 384, -1);
+    }
+    rec[((size_t)r * 6 + p.rn_c[node]) * 64 + lane] = node;
+    d.rec_mask |= 1 << p.rn_c[node];
   }
+  for (size_t q = 0; q < p.src_tg.size(); ++q) {
+    const auto &tg = p.src_tg[q];
+    if (tg.c >= 3) continue;                  // into H, before the step or by the H update
+    int &r = stab[(size_t)at(tg.idx, 0, lane) * p.ns + tg.s];
+    if (r < 0) {
+      r = (int)(src.size() / 192);
+      src.resize(src.size() + 192, -1);
+    }
+    src[((size_t)r * 3 + tg.c) * 64 + lane] = (int)q;
+  }
+  d.row_tab = upload_list(d, tab);
+  d.src_tab = upload_list(d, stab);
+  d.row_rec = upload_list(d, rec);
+  d.row_src = upload_list(d, src);
 }
 
 static void build_lists(Plan &p, Dev &d) {
@@ -4284,9 +4285,10 @@ static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bo
   window(A.nx, 64, L.xs, L.xn);
   window(A.ny, 1, L.ys, L.yn);
   window(A.nz, 1, L.zs, L.zn);
-  L.row_tab = d.row_tab[adj ? 1 : 0];
-  L.row_rec = d.row_rec[adj ? 1 : 0];
-  L.row_src = d.row_src[adj ? 1 : 0];
+  L.row_tab = d.row_tab;
+  L.src_tab = adj ? nullptr : d.src_tab;
+  L.row_rec = d.row_rec;
+  L.row_src = d.row_src;
   L.rec_mask = d.rec_mask;
   L.adj = adj ? 1 : 0;
   const int *box = d.ent_box[adj ? 1 : 0];
