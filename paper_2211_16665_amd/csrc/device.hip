@@ -1029,8 +1029,7 @@ __device__ __forceinline__ T curl_update(T f, T c, T a1, T a0, T s1, bool p1, T 
 
 template <typename T>
 struct LeapArgs {
-  const T *fi, *pi;                  // fields and CPML memory: the half the step reads,
-  T *fo, *po, *pe;                   // the half it writes, and half 0 (memory of E)
+  T *f0, *f1, *p0, *p1;              // halves of the fields and of the CPML memory (E's: half 0)
   const T *ce, *axt;
   const AxRow<T> *axr;               // [3][LA]
   T *hist;                           // slot of this step's sample (HIST)
@@ -1056,6 +1055,23 @@ struct LeapArgs {
   int adj;                           // adjoint run: the E receiver nodes are the injections
   uint32_t ej, ejn, ek, ekn;         // first and number of the rows and planes they span
 };
+
+// The step a launch computes, from the counter in the workspace, and the
+// halves that it reads and writes: a captured launch may be replayed, and a
+// plan may step several workspaces in turn, so the host's count decides
+// nothing here.
+template <typename T>
+struct Place {
+  int n;
+  const T *fi, *pi;
+  T *fo, *po;
+};
+template <typename T>
+__device__ __forceinline__ Place<T> place_of(const LeapArgs<T> &L) {
+  const int n = L.step[0] + 1;
+  const bool odd = n & 1;
+  return {n, odd ? L.f1 : L.f0, odd ? L.p1 : L.p0, odd ? L.f0 : L.f1, odd ? L.p0 : L.p1};
+}
 
 // Block -> (64-node tile of x, row, plane, source) and the row's index, for
 // rows of waves: as tile_of with runs of blocks an XCD, without branches.  The
@@ -1086,15 +1102,18 @@ __device__ __forceinline__ void row_kind(const LeapArgs<T> &L, int i0, int j, in
   xl = (uint32_t)i0 - L.xs >= L.xn;
   yz = ((uint32_t)j - L.ys >= L.yn) | ((uint32_t)k - L.zs >= L.zn);
 }
-// The tables of a row, if any (rows outside the box of the entries do not ask)
+// The tables of a row, if any (rows outside the box of the entries do not
+// ask); n: the step, past the run's last one nothing is injected or recorded
+// (tested last, so that the counter and the tables are in flight together)
 template <typename T>
-__device__ __forceinline__ int2 row_tables(const LeapArgs<T> &L, int b, int j, int k, int s) {
+__device__ __forceinline__ int2 row_tables(const LeapArgs<T> &L, int b, int j, int k, int s, int n,
+                                           int nt) {
   int2 row = make_int2(-1, -1);
   if (((uint32_t)j - L.ej < L.ejn) & ((uint32_t)k - L.ek < L.ekn)) {
     row.x = L.row_tab[b];
     if (L.src_tab) row.y = L.src_tab[b * L.ns + s];
   }
-  return row;
+  return n < nt ? row : make_int2(-1, -1);
 }
 
 // The lane's receiver nodes and injections.  A lane has at most one of each a
@@ -1171,15 +1190,15 @@ __device__ __forceinline__ void record_row(const StepArgs<T> &A, const RowEnt &e
 // XL: nodes of the wave may lie in an x layer or at an x wall; YZ: the row
 // may lie in a y or z layer or at a wall; ENT: it holds entries (row: its tables).
 template <typename T, bool HIST, bool NT, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int2 row,
-                                          int i0, int j, int k) {
+__device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T> &A, const Place<T> &P,
+                                          int s, int2 row, int i0, int j, int k) {
   // coefficients of the rows j, j - 1, k, k - 1 and of i0 - 1: read before
   // the marker below, so that they are scalar loads
   const bool j_lo = !YZ || j >= 1, k_lo = !YZ || k >= 1, left = !XL || i0 > 0;
   const int jm = j_lo ? j - 1 : j, km = k_lo ? k - 1 : k;
   const AxRow<T> yj = L.axr[L.LA + j], ym = L.axr[L.LA + jm], zk = L.axr[2 * L.LA + k],
                  zm = L.axr[2 * L.LA + km], xl = L.axr[left ? i0 - 1 : 0];
-  const int n = ENT ? L.step[0] + 1 : 0;
+  const int n = P.n;
   // each variant starts with its own marker: loads common to the variants
   // are not hoisted above the branches (that kept the registers of all of
   // them alive at once)
@@ -1197,7 +1216,7 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   const uint32_t x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz;
   const uint32_t q0 = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0;
   const int64_t so = (int64_t)s * L.F6;
-  const __amdgpu_buffer_rsrc_t rI = rsrc_of(L.fi + so), rC = rsrc_of(L.ce), rX = rsrc_of(L.axt);
+  const __amdgpu_buffer_rsrc_t rI = rsrc_of(P.fi + so), rC = rsrc_of(L.ce), rX = rsrc_of(L.axt);
   const uint32_t x = q0, y = q0 + L.Fb, z = y + L.Fb, u = z + L.Fb, v = u + L.Fb, w = v + L.Fb;
   // ---- loads: E^n at the node and the neighbours, H^{n-1/2}, dt/eps ----
   const T ex0 = bload<T>(rI, o, x), ey0 = bload<T>(rI, o, y), ez0 = bload<T>(rI, o, z);
@@ -1268,7 +1287,7 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   const uint32_t rZh = oZ + (uint32_t)(lzh * L.NY + j) * L.PXb;
   const uint32_t rZn = oZ + 2 * L.sZb + (uint32_t)(lzn * L.NY + j) * L.PXb;
   if constexpr (XL || YZ) {
-    const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.pi + sp), rE = rsrc_of(L.pe + sp);
+    const __amdgpu_buffer_rsrc_t rP = rsrc_of(P.pi + sp), rE = rsrc_of(L.p0 + sp);
     if constexpr (YZ) {
       if (py) {
         hx_y = bload<T>(rP, o, rYh);
@@ -1374,21 +1393,21 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   }
   // ---- stores ----
   const bool row_x = j_lo && k_lo, row_y = k_lo, row_z = j_lo;
-  const __amdgpu_buffer_rsrc_t rO = rsrc_of(L.fo + so);
+  const __amdgpu_buffer_rsrc_t rO = rsrc_of(P.fo + so);
   bstore<NT>(Hx, rO, o, u);
   bstore<NT>(Hy, rO, o, v);
   bstore<NT>(Hz, rO, o, w);
   if (row_x) bstore<NT>(e1x, rO, o, x);
   if (row_y) bstore<NT>(e1y, rO, o, y);
   if (row_z) bstore<NT>(e1z, rO, o, z);
-  if constexpr (HIST) {
+  if (HIST && n < A.nt) {
     const __amdgpu_buffer_rsrc_t rH = rsrc_of(L.hist + (int64_t)s * L.hist_src);
     if (row_x) bstore<NT>(e1x, rH, o, x);
     if (row_y) bstore<NT>(e1y, rH, o, y);
     if (row_z) bstore<NT>(e1z, rH, o, z);
   }
   if constexpr (XL || YZ) {
-    const __amdgpu_buffer_rsrc_t rQ = rsrc_of(L.po + sp), rE = rsrc_of(L.pe + sp);
+    const __amdgpu_buffer_rsrc_t rQ = rsrc_of(P.po + sp), rE = rsrc_of(L.p0 + sp);
     if constexpr (YZ) {
       // memory outside a component's lattice reaches no result
       if (py) {
@@ -1423,24 +1442,25 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
 
 template <typename T, bool HIST, bool NT>
 __global__ void __launch_bounds__(64) k_leap(LeapArgs<T> L, StepArgs<T> A) {
+  const Place<T> P = place_of(L);
   int bx, j, k, s;
   const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
-  const int2 row = row_tables(L, b, j, k, s);
+  const int2 row = row_tables(L, b, j, k, s, P.n, A.nt);
   if (max(row.x, row.y) >= 0)
-    leap_wave<T, HIST, NT, true, true, true>(L, A, s, row, i0, j, k);
+    leap_wave<T, HIST, NT, true, true, true>(L, A, P, s, row, i0, j, k);
   else if (xl) {
-    if (yz) leap_wave<T, HIST, NT, true, true, false>(L, A, s, row, i0, j, k);
-    else leap_wave<T, HIST, NT, true, false, false>(L, A, s, row, i0, j, k);
+    if (yz) leap_wave<T, HIST, NT, true, true, false>(L, A, P, s, row, i0, j, k);
+    else leap_wave<T, HIST, NT, true, false, false>(L, A, P, s, row, i0, j, k);
   } else {
-    if (yz) leap_wave<T, HIST, NT, false, true, false>(L, A, s, row, i0, j, k);
-    else leap_wave<T, HIST, NT, false, false, false>(L, A, s, row, i0, j, k);
+    if (yz) leap_wave<T, HIST, NT, false, true, false>(L, A, P, s, row, i0, j, k);
+    else leap_wave<T, HIST, NT, false, false, false>(L, A, P, s, row, i0, j, k);
   }
   // last: a store before them would turn the uniform loads into vector ones
-  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = L.step[0] + 1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = P.n;
 }
 
 // ---------------------------------------------------------------------------
@@ -1639,8 +1659,8 @@ __device__ __forceinline__ T d4(T a, T b, T c, T d) {
 }
 
 template <typename T, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int b, int i0,
-                                        int j, int k) {
+__device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, const Place<T> &P, int s, int b,
+                                        int i0, int j, int k) {
   const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];   // scalar loads: before the marker
   asm volatile("; h4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));            // see leap_wave
   const int tid = threadIdx.x, i = i0 + tid;
@@ -1662,7 +1682,7 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
                  qjd = (uint32_t)k * L.PLb + (uint32_t)jd * L.PXb + x0;
   const uint32_t qka = (uint32_t)ka * L.PLb + (uint32_t)j * L.PXb + x0, qkc = q + L.PLb,
                  qkd = (uint32_t)kd * L.PLb + (uint32_t)j * L.PXb + x0;
-  const __amdgpu_buffer_rsrc_t rI = rsrc_of(L.fi + (int64_t)s * L.F6), rX = rsrc_of(L.axt);
+  const __amdgpu_buffer_rsrc_t rI = rsrc_of(P.fi + (int64_t)s * L.F6), rX = rsrc_of(L.axt);
   const T ex = bload<T>(rI, o, q), ey = bload<T>(rI, o, q + Fb), ez = bload<T>(rI, o, q + 2 * Fb);
   T ex_ja = bload<T>(rI, o, qja), ez_ja = bload<T>(rI, o, qja + 2 * Fb);
   const T ex_jc = bload<T>(rI, o, qjc), ez_jc = bload<T>(rI, o, qjc + 2 * Fb);
@@ -1708,7 +1728,7 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   const uint32_t rYh = L.oYb + x0 + (uint32_t)(k * W + lyh) * L.PXb;
   const uint32_t rZh = L.oZb + x0 + (uint32_t)(lzh * L.NY + j) * L.PXb;
   if constexpr (XL || YZ) {
-    const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.pi + sp);
+    const __amdgpu_buffer_rsrc_t rP = rsrc_of(P.pi + sp);
     if (YZ && py) {
       hx_y = bload<T>(rP, o, rYh);
       hz_y = bload<T>(rP, o, rYh + L.sYb);
@@ -1725,7 +1745,7 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
     }
   }
   if constexpr (ENT) {
-    const int n = L.step[0] + 1;
+    const int n = P.n;
     int lo, hi;
     entry_slice_at(A, b, n, tid, lo, hi);
     if (lo < hi) {
@@ -1754,12 +1774,12 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
                                    d4(ez_ia, ez, ez_ic, ez_id), zero, ih, px, hy_x, xh);
   const T Hz = curl_update<XL, YZ>(hz, mc, d4(ey_ia, ey, ey_ic, ey_id), zero, ih, px, hz_x, xh,
                                    d4(ex_ja, ex, ex_jc, ex_jd), zero, yj.ih, py, hz_y, yh);
-  const __amdgpu_buffer_rsrc_t rO = rsrc_of(L.fo + (int64_t)s * L.F6);
+  const __amdgpu_buffer_rsrc_t rO = rsrc_of(P.fo + (int64_t)s * L.F6);
   bstore<false>(Hx, rO, o, q + 3 * Fb);
   bstore<false>(Hy, rO, o, q + 4 * Fb);
   bstore<false>(Hz, rO, o, q + 5 * Fb);
   if constexpr (XL || YZ) {
-    const __amdgpu_buffer_rsrc_t rQ = rsrc_of(L.po + sp);
+    const __amdgpu_buffer_rsrc_t rQ = rsrc_of(P.po + sp);
     if (YZ && py) {
       bstore<false>(hx_y, rQ, o, rYh);
       bstore<false>(hz_y, rQ, o, rYh + L.sYb);
@@ -1776,10 +1796,10 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
 }
 
 template <typename T, bool HIST, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, int s, int2 row, int i0,
-                                        int j, int k) {
+__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, const Place<T> &P, int s, int2 row,
+                                        int i0, int j, int k) {
   const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];
-  const int n = ENT ? L.step[0] + 1 : 0;
+  const int n = P.n;
   asm volatile("; e4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));
   const int tid = threadIdx.x, i = i0 + tid;
   RowEnt ent;
@@ -1806,7 +1826,7 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   const uint32_t qka = (uint32_t)ka * L.PLb + rj + x0, qkb = (uint32_t)kb * L.PLb + rj + x0,
                  qkd = (uint32_t)kd * L.PLb + rj + x0;
   const int64_t so = (int64_t)s * L.F6;
-  const __amdgpu_buffer_rsrc_t rI = rsrc_of(L.fi + so), rO = rsrc_of(L.fo + so), rC = rsrc_of(L.ce),
+  const __amdgpu_buffer_rsrc_t rI = rsrc_of(P.fi + so), rO = rsrc_of(P.fo + so), rC = rsrc_of(L.ce),
                                rX = rsrc_of(L.axt);
   const uint32_t fx = 3 * Fb, fy = 4 * Fb, fz = 5 * Fb;
   const T hx = bload<T>(rO, o, q + fx), hy = bload<T>(rO, o, q + fy), hz = bload<T>(rO, o, q + fz);
@@ -1852,7 +1872,7 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   }
   T ex_y = T(0), ex_z = T(0), ey_z = T(0), ey_x = T(0), ez_x = T(0), ez_y = T(0);
   Stretch<T> xn{};
-  const __amdgpu_buffer_rsrc_t rE = rsrc_of(L.pe + (int64_t)s * L.psi_src);
+  const __amdgpu_buffer_rsrc_t rE = rsrc_of(L.p0 + (int64_t)s * L.psi_src);
   const uint32_t r0 = (uint32_t)(k * L.NY + j) * (uint32_t)W * sz + 2 * L.sXb;
   const uint32_t rYn = L.oYb + x0 + 2 * L.sYb + (uint32_t)(k * W + lyn) * L.PXb;
   const uint32_t rZn = L.oZb + x0 + 2 * L.sZb + (uint32_t)(lzn * L.NY + j) * L.PXb;
@@ -1898,7 +1918,7 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   if (row_x) bstore<false>(e1x, rO, o, q);
   if (row_y) bstore<false>(e1y, rO, o, q + Fb);
   if (row_z) bstore<false>(e1z, rO, o, q + 2 * Fb);
-  if constexpr (HIST) {
+  if (HIST && n < A.nt) {
     const __amdgpu_buffer_rsrc_t rH = rsrc_of(L.hist + (int64_t)s * L.hist_src);
     if (row_x) bstore<false>(e1x, rH, o, q);
     if (row_y) bstore<false>(e1y, rH, o, q + Fb);
@@ -1920,6 +1940,7 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
 
 template <typename T, bool INJ>
 __global__ void __launch_bounds__(64) k_rows_h4(LeapArgs<T> L, StepArgs<T> A) {
+  const Place<T> P = place_of(L);
   int bx, j, k, s;
   const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
@@ -1927,35 +1948,36 @@ __global__ void __launch_bounds__(64) k_rows_h4(LeapArgs<T> L, StepArgs<T> A) {
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
   if (INJ && A.tile_tab[b] >= 0)
-    h4_wave<T, true, true, true>(L, A, s, b, i0, j, k);
+    h4_wave<T, true, true, true>(L, A, P, s, b, i0, j, k);
   else if (xl) {
-    if (yz) h4_wave<T, true, true, false>(L, A, s, b, i0, j, k);
-    else h4_wave<T, true, false, false>(L, A, s, b, i0, j, k);
+    if (yz) h4_wave<T, true, true, false>(L, A, P, s, b, i0, j, k);
+    else h4_wave<T, true, false, false>(L, A, P, s, b, i0, j, k);
   } else {
-    if (yz) h4_wave<T, false, true, false>(L, A, s, b, i0, j, k);
-    else h4_wave<T, false, false, false>(L, A, s, b, i0, j, k);
+    if (yz) h4_wave<T, false, true, false>(L, A, P, s, b, i0, j, k);
+    else h4_wave<T, false, false, false>(L, A, P, s, b, i0, j, k);
   }
 }
 
 template <typename T, bool HIST>
 __global__ void __launch_bounds__(64) k_rows_e4(LeapArgs<T> L, StepArgs<T> A) {
+  const Place<T> P = place_of(L);
   int bx, j, k, s;
   const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
-  const int2 row = row_tables(L, b, j, k, s);
+  const int2 row = row_tables(L, b, j, k, s, P.n, A.nt);
   if (max(row.x, row.y) >= 0)
-    e4_wave<T, HIST, true, true, true>(L, A, s, row, i0, j, k);
+    e4_wave<T, HIST, true, true, true>(L, A, P, s, row, i0, j, k);
   else if (xl) {
-    if (yz) e4_wave<T, HIST, true, true, false>(L, A, s, row, i0, j, k);
-    else e4_wave<T, HIST, true, false, false>(L, A, s, row, i0, j, k);
+    if (yz) e4_wave<T, HIST, true, true, false>(L, A, P, s, row, i0, j, k);
+    else e4_wave<T, HIST, true, false, false>(L, A, P, s, row, i0, j, k);
   } else {
-    if (yz) e4_wave<T, HIST, false, true, false>(L, A, s, row, i0, j, k);
-    else e4_wave<T, HIST, false, false, false>(L, A, s, row, i0, j, k);
+    if (yz) e4_wave<T, HIST, false, true, false>(L, A, P, s, row, i0, j, k);
+    else e4_wave<T, HIST, false, false, false>(L, A, P, s, row, i0, j, k);
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = L.step[0] + 1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.step_w[0] = P.n;
 }
 
 // ---------------------------------------------------------------------------
@@ -2829,7 +2851,7 @@ __device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T), x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
   const uint32_t q = (uint32_t)k * L.PLb + (uint32_t)j * L.PXb + x0, qj = q + L.PXb, qk = q + L.PLb;
-  const __amdgpu_buffer_rsrc_t rA = rsrc_of(L.fi + (int64_t)s * L.F6), rO = rsrc_of(L.fo + (int64_t)s * L.F6),
+  const __amdgpu_buffer_rsrc_t rA = rsrc_of(L.f0 + (int64_t)s * L.F6), rO = rA,
                                rC = rsrc_of(L.ce), rX = rsrc_of(L.axt);
   const T ax = bload<T>(rA, o, q), ay = bload<T>(rA, o, q + Fb), az = bload<T>(rA, o, q + 2 * Fb);
   const T ax_j = bload<T>(rA, o, qj), az_j = bload<T>(rA, o, qj + 2 * Fb);
@@ -2870,7 +2892,7 @@ __device__ __forceinline__ void td_e_wave(const LeapArgs<T> &L, const StepArgs<T
     nxr = right && pml_int(i0 + 64, L.nx, npml, lxr);
   }
   const int64_t sp = (int64_t)s * L.psi_src;
-  const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.pe + sp);
+  const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.p0 + sp);
   const uint32_t r0 = (uint32_t)(k * L.NY + j) * (uint32_t)W * sz;
   const uint32_t oY = L.oYb + x0, oZ = L.oZb + x0;
   auto rowY = [&](int l) { return oY + (uint32_t)(k * W + l) * L.PXb; };
@@ -2982,7 +3004,7 @@ __device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T
   const uint32_t qj = j_lo ? q - L.PXb : q, qk = k_lo ? q - L.PLb : q;
   const bool i_lo = !XL || i >= 1;
   const bool okx = j_lo && k_lo, oky = i_lo && k_lo, okz = i_lo && j_lo;
-  const __amdgpu_buffer_rsrc_t rA = rsrc_of(L.fi + (int64_t)s * L.F6), rO = rsrc_of(L.fo + (int64_t)s * L.F6),
+  const __amdgpu_buffer_rsrc_t rA = rsrc_of(L.f0 + (int64_t)s * L.F6), rO = rA,
                                rC = rsrc_of(L.ce), rX = rsrc_of(L.axt);
   const T hx = bload<T>(rA, o, q + 3 * Fb), hy = bload<T>(rA, o, q + 4 * Fb), hz = bload<T>(rA, o, q + 5 * Fb);
   const T hx_j = bload<T>(rA, o, qj + 3 * Fb), hz_j = bload<T>(rA, o, qj + 5 * Fb);
@@ -3027,7 +3049,7 @@ __device__ __forceinline__ void td_h_wave(const LeapArgs<T> &L, const StepArgs<T
     cxn = (uint32_t)(i < npml ? i : i - L.nx + W - 1) * sz;
     hxl = left && pml_half(i0 - 1, L.nx, npml, lxl);
   }
-  const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.pe + (int64_t)s * L.psi_src);
+  const __amdgpu_buffer_rsrc_t rP = rsrc_of(L.p0 + (int64_t)s * L.psi_src);
   const uint32_t r0 = (uint32_t)(k * L.NY + j) * (uint32_t)W * sz;
   const uint32_t oY = L.oYb + x0, oZ = L.oZb + x0;
   auto rowY = [&](int l) { return oY + (uint32_t)(k * W + l) * L.PXb; };
@@ -3133,7 +3155,7 @@ __global__ void __launch_bounds__(64) k_rows_td_e(LeapArgs<T> L, StepArgs<T> A, 
   row_kind(L, i0, j, k, xl, yz);
   // z: null where no magnetic receiver is recorded
   int2 row = make_int2(-1, -1);
-  if (z) row = row_tables(L, b, j, k, s);
+  if (z) row = row_tables(L, b, j, k, s, 0, 1);
   if (max(row.x, row.y) >= 0)
     td_e_wave<T, true, true, true>(L, A, s, row, i0, j, k, C, z);
   else if (xl) {
@@ -3156,7 +3178,7 @@ __global__ void __launch_bounds__(64) k_rows_td_h(LeapArgs<T> L, StepArgs<T> A, 
   row_kind(L, i0, j, k, xl, yz);
   // z: null at the first step (no sample before it)
   int2 row = make_int2(-1, -1);
-  if (z) row = row_tables(L, b, j, k, s);
+  if (z) row = row_tables(L, b, j, k, s, 0, 1);
   if (max(row.x, row.y) >= 0)
     td_h_wave<T, true, true, true>(L, A, s, row, i0, j, k, Enew, Eold, tdw, C, z);
   else if (xl) {
@@ -4232,18 +4254,17 @@ static void launch_step(const StepArgs<T> &A, bool hist, dim3 grid, dim3 block, 
   else go(k_step<T, false>, grid, block, lds, st, kt, A);
 }
 
-// n: the step (the host's count); past the run's last step nothing is
-// injected, recorded or kept.  keep: E^{n+1} of every source also goes there,
+// n: the step by the host's count, which places the sample in its transform
+// block and nothing else.  keep: E^{n+1} of every source also goes there,
 // [ns][3][F] (runs without a volume transform)
 template <typename T>
 static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bool adj, int n,
                              T *keep = nullptr) {
   LeapArgs<T> L{};
-  L.fi = A.fields + ((n & 1) ? A.fbuf : 0);
-  L.fo = A.fields + ((n & 1) ? 0 : A.fbuf);
-  L.pi = A.psi + ((n & 1) ? A.pbuf : 0);
-  L.po = A.psi + ((n & 1) ? 0 : A.pbuf);
-  L.pe = A.psi;
+  L.f0 = A.fields;
+  L.f1 = A.fields + A.fbuf;
+  L.p0 = A.psi;
+  L.p1 = A.psi + A.pbuf;
   L.ce = A.ce;
   L.axt = A.axt;
   L.axr = static_cast<const AxRow<T> *>(d.axr);
@@ -4293,11 +4314,11 @@ static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bo
   L.adj = adj ? 1 : 0;
   const int *box = d.ent_box[adj ? 1 : 0];
   L.ej = (uint32_t)box[0];
-  L.ejn = n < p.nt ? (uint32_t)std::max(0, box[1] - box[0] + 1) : 0;
+  L.ejn = (uint32_t)std::max(0, box[1] - box[0] + 1);
   L.ek = (uint32_t)box[2];
   L.ekn = (uint32_t)std::max(0, box[3] - box[2] + 1);
   const int D = adj ? 1 : p.dec, m = n + 1, r = m / D & (p.kb - 1);
-  const bool hist = vol && n < p.nt && m % D == 0 && r != 0;
+  const bool hist = vol && m % D == 0 && r != 0;
   if (hist) L.hist = A.hist + (int64_t)(r - 1) * 3 * A.F;
   if (keep) {
     L.hist = keep;
@@ -4400,7 +4421,7 @@ static void enqueue_step(Plan &p, Dev &d, const WS &w, void *vol, bool adj, hipS
     if (o4 && wave_rows(p)) {
       const LeapArgs<T> L = leap_args<T>(p, d, A, vol != nullptr, adj, n, keep);
       const dim3 row(64);
-      if (hinj && n < p.nt) go(k_rows_h4<T, true>, grid, row, 0, st, kh, L, Ah);
+      if (hinj) go(k_rows_h4<T, true>, grid, row, 0, st, kh, L, Ah);
       else go(k_rows_h4<T, false>, grid, row, 0, st, kh, L, Ah);
       if (L.hist) go(k_rows_e4<T, true>, grid, row, 0, st, ke, L, A);
       else go(k_rows_e4<T, false>, grid, row, 0, st, ke, L, A);
@@ -4595,12 +4616,12 @@ static void run_steps_t(Plan &p, Dev &d, const WS &w, void *vol, bool adj, int n
     }
     HIP_CHECK(hipGetLastError());
   };
-  if (K < 2 || nsteps < K || p.host_step + K > p.nt) {
+  if (K < 2 || nsteps < K) {
     for (int t = 0; t < nsteps; ++t) eager(1, sample > 0 && t % sample == 0);
     return;
   }
   // graph of K steps, captured on a private stream and replayed on st
-  const int phase = p.host_step % (p.kb * D) * 2 + (p.host_step & 1);
+  const int phase = p.host_step % (p.kb * D);
   char key[256];
   snprintf(key, sizeof key, "%p/%p/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%llu/%llu", w.fields,
            vol, (int)adj, K, phase, p.bx, p.by, p.xcd, p.kb * 64 + D, p.vx, p.vxh, p.sched, p.kz, p.order,
@@ -4631,8 +4652,7 @@ static void run_steps_t(Plan &p, Dev &d, const WS &w, void *vol, bool adj, int n
   // replay the graph
   const int every = sample > 0 ? std::max(1, sample / K) : 0;
   int done = 0, chunk = 0;
-  // a replay holds no step past the run's last one (those take other launches)
-  while (nsteps - done >= K && p.host_step + K <= std::max(p.nt, 0)) {
+  while (nsteps - done >= K) {
     if (every && chunk % every == 0) {
       eager(K, true);
     } else {
