@@ -4704,6 +4704,7 @@ static void collect_kernel_stats(Dev &d) {
 // flush).
 static void zero_state(Plan &p, const WS &w, void *ws, int mode, hipStream_t st) {
   p.host_step = 0;
+  p.host_ws = ws;
   char *b = static_cast<char *>(ws);
   zero_bytes(b, p.core_state_bytes(), st);
   zero_bytes(b + p.state_bytes(), p.workspace_bytes(mode) - p.state_bytes(), st);
@@ -4767,6 +4768,28 @@ static void check_finite(const double2 *dptr, size_t n, const int *flag_dev, hip
   if (bad) fail(FWD_ERR_NONFINITE, "non-finite field: unstable run (dt above the CFL bound?)");
 }
 
+// The host's step count from a workspace's counters (last completed step: the
+// larger of the two).  Waits for the stream.
+static void read_host_step(Plan &p, const void *ws, hipStream_t st) {
+  int cnt[2] = {0, 0};
+  const WS w = carve(p, const_cast<void *>(ws));
+  HIP_CHECK(hipMemcpyAsync(cnt, w.step, sizeof cnt, hipMemcpyDeviceToHost, st));
+  HIP_CHECK(hipStreamSynchronize(st));
+  p.host_step = std::max(cnt[0], cnt[1]) + 1;
+  p.host_ws = ws;
+}
+
+// The host's count decides which steps of a run with a volume close a
+// transform block: where it was taken on another workspace (a plan may step
+// several in turn) it is read again.  A stream that is being captured cannot
+// be waited for; there the count stands.
+static void follow_workspace(Plan &p, const void *ws, const void *vol, hipStream_t st) {
+  if (!vol || ws == p.host_ws) return;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  HIP_CHECK(hipStreamIsCapturing(st, &cs));
+  if (cs == hipStreamCaptureStatusNone) read_host_step(p, ws, st);
+}
+
 // ---------------------------------------------------------------------------
 // entry points used by the C ABI
 // ---------------------------------------------------------------------------
@@ -4782,6 +4805,7 @@ void dev_run_steps(Plan &p, void *ws, void *vol, int nsteps, void *stream) {
   ensure_tables(p, st);
   if (nsteps < 0 || nsteps > p.nt) fail(FWD_ERR_INVALID_ARG, "nsteps outside [0, nt]");
   Dev &d = D(p);
+  follow_workspace(p, ws, vol, st);
   run_steps_any(p, d, carve(p, ws), vol, false, nsteps, st);
   check_abort(p, carve(p, ws), st);
 }
@@ -4801,6 +4825,7 @@ void dev_run_receivers(Plan &p, void *ws, double *E_rec, void *stream) {
 void dev_run_flush(Plan &p, void *ws, void *vol, void *stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   ensure_tables(p, st);
+  follow_workspace(p, ws, vol, st);
   flush_any(p, D(p), carve(p, ws), vol, false, st);
 }
 
@@ -4919,13 +4944,7 @@ void dev_checkpoint(Plan &p, const void *ws, const void *vol, void *snap, int sa
     if (vol)
       HIP_CHECK(hipMemcpyAsync(const_cast<void *>(vol), sn + sb, p.volume_bytes(),
                                hipMemcpyDeviceToDevice, st));
-    // the host's step count follows the restored counters (last completed
-    // step: the larger of the two)
-    int cnt[2] = {0, 0};
-    const WS w = carve(p, const_cast<void *>(ws));
-    HIP_CHECK(hipMemcpyAsync(cnt, w.step, sizeof cnt, hipMemcpyDeviceToHost, st));
-    HIP_CHECK(hipStreamSynchronize(st));
-    p.host_step = std::max(cnt[0], cnt[1]) + 1;
+    read_host_step(p, ws, st);             // follows the restored counters
   }
 }
 
@@ -5277,6 +5296,7 @@ double dev_autotune(Plan &p, void *ws, size_t ws_bytes, void *vol, size_t vol_by
   // history out further); between candidates only the step counters and
   // the flush marker are reset (stepping on from any state costs the same)
   HIP_CHECK(hipMemsetAsync(ws, 0, ws_bytes, st));
+  p.host_ws = ws;
   if (vol && !adj) HIP_CHECK(hipMemsetAsync(vol, 0, p.volume_bytes(), st));
   auto time_cand = [&](const TuneCand &c, int nsteps) {
     apply_cand(p, c);

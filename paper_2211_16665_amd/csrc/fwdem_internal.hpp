@@ -134,6 +134,7 @@ struct Plan {
   double last_ms = 0;
   int last_steps = 0;
   int host_step = 0;          // steps completed in the current run (the device counters' value + 1)
+  const void *host_ws = nullptr;   // the workspace that host_step was counted on
 
   int64_t plane() const { return (int64_t)NY * PX; }
   int64_t field_elems() const { return (int64_t)NZ * NY * PX; }

@@ -135,3 +135,36 @@ def test_steps_past_the_end_add_nothing(form):
     p.use_workspace(a)
     p.run_steps(41)
     assert np.array_equal(receivers(p), E)
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("between", [2, "full"])
+def test_volumes_of_two_workspaces(form, between):
+    """The steps that close a transform block follow the workspace: a run with
+    a volume left inside a block, another one between, then on to the end."""
+    p, _ = plan(*form)
+    say(f"volumes of two workspaces, {between} steps between", form)
+    nt, ref = p.info.nt, p.volume_buffer()
+    p.forward(vol=ref, want_volume=True)
+    ref = p.volume_export(ref).cpu().numpy()
+    a, b, va, vb = buffer(p), buffer(p), p.volume_buffer(), p.volume_buffer()
+    p.use_workspace(a)
+    p.run_begin(va)
+    p.run_steps(13, va)
+    p.use_workspace(b)
+    if between == "full":
+        p.forward(vol=vb, want_volume=True)
+    else:
+        p.run_begin(vb)
+        p.run_steps(between, vb)
+    p.use_workspace(a)
+    p.run_steps(nt - 13, va)
+    if between != "full":
+        p.use_workspace(b)
+        p.run_steps(nt - between, vb)
+    p.use_workspace(a)
+    p.run_flush(va)
+    p.use_workspace(b)
+    p.run_flush(vb)
+    for v in (va, vb):
+        assert np.array_equal(p.volume_export(v).cpu().numpy(), ref)
