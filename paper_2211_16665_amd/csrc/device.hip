@@ -3852,11 +3852,13 @@ struct Tiling {
 // 200x200x100 with 4 sources 546 against 381; FP64: 32x32x32 13.3 against
 // 8.2, 128x128x96 113 against 85; order 4, FP32, 101x101x61: 35.6 against
 // 23.6); at order 2 their 16-byte vector forms remain a choice of the caller.
-static bool wave_rows(const Plan &p) {
+static bool rows_fit(const Plan &p) {
   const uint64_t lim = (uint64_t)1 << 32;
-  return p.sched == 0 && p.vx == 1 && p.vxh == 1 && !p.h_on_walls &&
-         6 * (uint64_t)p.field_elems() * p.tsize() < lim &&
+  return !p.h_on_walls && 6 * (uint64_t)p.field_elems() * p.tsize() < lim &&
          (uint64_t)p.psi_elems_per_source() * p.tsize() < lim;
+}
+static bool wave_rows(const Plan &p) {
+  return p.sched == 0 && p.vx == 1 && p.vxh == 1 && rows_fit(p);
 }
 static bool one_launch(const Plan &p) { return p.fd_order == 2 && wave_rows(p); }
 
@@ -5276,9 +5278,10 @@ double dev_autotune(Plan &p, void *ws, size_t ws_bytes, void *vol, size_t vol_by
     p.kb = keep;
   }
   char key[256];
-  snprintf(key, sizeof key, "%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d", p.nx, p.ny,
+  snprintf(key, sizeof key, "%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d", p.nx, p.ny,
            p.nz, p.npml, p.ns, p.nf(), p.dtype, p.acc, p.fd_order, mode, vol ? 1 : 0,
-           (int)kbs.size(), (int)p.rn_c.size(), steps, adj ? 1 : p.dec, p.stream_stores);
+           (int)kbs.size(), (int)p.rn_c.size(), steps, adj ? 1 : p.dec, p.stream_stores,
+           rows_fit(p) ? 1 : 0, p.src_kind);
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune_cache.find(key);
