@@ -414,15 +414,17 @@ fwd_status fwd_set_option(fwd_plan *plan, int key, double value);
 fwd_status fwd_get_option(const fwd_plan *plan, int key, double *value);
 
 /* Self-written tile/schedule autotuner.  A staged search on the given
- * buffers: the one-launch step, or where it does not apply block shape, then
- * vector widths; then tile order and XCD remap,
- * then the fused schedule (shapes, planes per block), then the transform
+ * buffers: the one-launch step (order 4: its two kernels, a wave a row), or
+ * where it does not apply the block shape of the two kernels; then their
+ * 16-byte vectors (order 2); then tile order and XCD remap, then the fused
+ * schedule (shapes, planes per block), then the transform
  * block FWD_OPT_DFT_BLOCK in {8, 16, 32} when vol_dev is given and ws_bytes holds
  * the workspace of the longer block.  Each candidate runs `steps` steps of
  * the given mode untimed (graph capture) and then the same number timed; the
  * fastest is kept (as options of the plan) and its time per step (ms)
  * returned.  Results are cached for the life of the process, keyed by the
- * grid, sources, frequencies, precisions, order, mode and `steps`: a second
+ * grid, sources and their kind, frequencies, precisions, order, mode, `steps`
+ * and whether the one-launch step applies: a second
  * call with the same key only applies the cached choice.  The state in
  * ws/vol is clobbered.  The workspace size may change with the transform
  * block: query fwd_workspace_size again before the next run.  */

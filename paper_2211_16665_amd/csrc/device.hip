@@ -5221,10 +5221,10 @@ void dev_adjoint_td(Plan &p, void *ws, size_t ws_bytes, void *scratch, size_t sc
 
 // ---------------------------------------------------------------------------
 // autotuner: time candidate schedules and tilings on the real buffers.  A
-// staged search (coordinate descent) instead of the full product: the
-// one-launch step, or where it does not apply block shape and vector widths; tile order x XCD remap; the fused schedule's shapes
-// and planes per block; the transform block K (8 or 16, when the workspace
-// holds the longer history).  Each candidate first runs `steps` steps
+// staged search (coordinate descent) instead of the full product: the rows of
+// waves, or where they do not apply block shapes; vector widths; tile order x
+// XCD remap; the fused schedule's shapes and planes per block; the transform
+// block K (8 or 16, when the workspace holds the longer history).  Each candidate first runs `steps` steps
 // untimed (its HIP graph is captured and instantiated there), then the same
 // number timed, so the timed interval holds the replays only.  Results are
 // cached for the process, keyed by everything that shapes the work.
@@ -5328,9 +5328,9 @@ double dev_autotune(Plan &p, void *ws, size_t ws_bytes, void *vol, size_t vol_by
       best_ms = ms;
       best = c;
     }
+    return ms;
   };
-  // stage 1: rows of waves, which have no shape to choose (at order 2 the two
-  // kernels' vector forms were slower wherever they apply); otherwise block
+  // stage 1: rows of waves, which have no shape to choose; otherwise block
   // shapes of the two kernels, one node per thread
   const int shapes[][2] = {{64, 4}, {64, 2}, {64, 1}, {32, 8}, {32, 4}, {16, 16},
                            {16, 8}, {16, 4}, {128, 2}, {256, 1}};
@@ -5347,15 +5347,37 @@ double dev_autotune(Plan &p, void *ws, size_t ws_bytes, void *vol, size_t vol_by
       consider(c);
     }
   }
-  // stage 2: 16-byte vectors (H only, then both)
-  if (!o4 && !leap) {
-    const TuneCand base = best;
-    for (int v : {1, 2}) {
+  // stage 2: 16-byte vectors (both updates, then H only).  Where stage 1 had
+  // no shapes, on each of them, and the best with the other remap: the pair
+  // loses to the one-launch step on every FP32 grid measured and up to some
+  // 10^7 FP64 nodes, and gains beyond (us a step, one launch against the best
+  // pair: 101x101x61 FP32 16 and 27, 400x400x200 FP32 with 8 sources 4350 and
+  // 5040; FP64: 128x128x96 61 and 69, 300x300x200 with 2 sources 1430 and
+  // 1200, 400x400x200 1290 and 1080).
+  if (!o4) {
+    TuneCand pair = best;
+    pair.vxh = pair.vx = 4;
+    double pair_ms = 1e300;
+    const TuneCand base = pair;
+    for (size_t q = 0; q < (leap ? std::size(shapes) : 1); ++q) {
       TuneCand c = base;
-      c.vxh = 4;
-      c.vx = v == 2 ? 4 : 1;
-      consider(c);
+      if (leap) {
+        c.bx = shapes[q][0];
+        c.by = shapes[q][1];
+      }
+      const double ms = consider(c);
+      if (ms < pair_ms) {
+        pair_ms = ms;
+        pair = c;
+      }
     }
+    if (leap) {                          // stage 3 sees the better form only
+      TuneCand c = pair;
+      c.xcd ^= 1;
+      if (consider(c) < pair_ms) pair = c;
+    }
+    pair.vx = 1;
+    consider(pair);
   }
   // stage 3: tile order and XCD remap
   {
