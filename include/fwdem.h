@@ -305,7 +305,9 @@ fwd_status fwd_adjoint(fwd_plan *plan, void *ws_dev, size_t ws_bytes,
  * fwd_adjoint (eq. gradsigmaij) it is exact inside the CPML layers too.
  *   ws_dev       forward workspace, fwd_workspace_size(FWD_MODE_FORWARD)
  *   scratch_dev  fwd_adjoint_td_size(segment) bytes of device memory
- *                (checkpoints, the E of one segment, adjoint state)
+ *                (checkpoints, the E of one segment, adjoint state).  The
+ *                first call after a model change also allocates the edges'
+ *                weights, 24 bytes a node, with the plan's device tables
  *   segment      steps between checkpoints (>= 1)
  *   resid_dev    complex [nsrc][nrec][ncomp][nfreq], W^2 (d - E)
  *   grad_dev     double [nz][ny][nx], added to if accumulate != 0

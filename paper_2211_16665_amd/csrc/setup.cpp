@@ -49,7 +49,6 @@ size_t Plan::td_scratch_bytes(int segment) const {
   b += align256((size_t)ns * psi_elems_per_source() * tsize());          // adjoint CPML
   b += align256((size_t)ns * 3 * F * 8);                                 // gradient products
   b += align256((size_t)ns * rn_c.size() * nf() * 16);                   // sensitivities
-  b += align256(3 * F * 8);                                              // edge weights
   return b;
 }
 
