@@ -1169,7 +1169,7 @@ template <int C, typename T>
 __device__ __forceinline__ void record_row(const StepArgs<T> &A, const RowEnt &e, int s, const double2 *z,
                                            const double (&v)[3]) {
   if (max(e.node[C], max(e.node[C + 1], e.node[C + 2])) < 0) return;
-  double2 *__restrict__ a[3];
+  double2 *a[3];                         // absent components point at node 0
 #pragma unroll
   for (int c = 0; c < 3; ++c) a[c] = A.racc + ((int64_t)s * A.nn + max(e.node[C + c], 0)) * A.nf;
 #pragma unroll 2
