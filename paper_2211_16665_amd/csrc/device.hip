@@ -147,17 +147,9 @@ struct StepArgs {
 // or z fastest, t = (by * nbx + bx) * nbz + bz (order 1: the blocks of
 // consecutive planes of a column tile run side by side, so the plane
 // neighbours a stencil reads are still in L2).  Returns the tile index.
-// Rows of waves (row_of): each XCD takes runs of 128
-// consecutive b, dealt round-robin, and the blocks past the last whole round
-// stay where they are.  Rows of a run still share their neighbours in one L2,
-// and every XCD gets its part of the layers, whose rows cost twice as much:
-// with one contiguous range per XCD the XCDs of the outermost planes finish
-// last (101x101x61, 4 sources: 53.5 us a step against 47.5 with runs and 47.3
-// unmapped; 1 source: 17.5, 17.2 and 19.7; runs of 16 to 1024 within 4 %).
-enum { XCD_RUN_LOG2 = 7 };
-template <typename Args>
-__device__ __forceinline__ int tile_of_b(const Args &A, uint32_t b, int &bx, int &by, int &bz,
-                                         int &s) {
+template <typename T>
+__device__ __forceinline__ int tile_of_b(const StepArgs<T> &A, uint32_t b, int &bx, int &by,
+                                         int &bz, int &s) {
   if (A.xcd) {
     const uint32_t q = (uint32_t)A.nblocks >> 3, r = (uint32_t)A.nblocks & 7u;
     const uint32_t x = b & 7u, local = b >> 3;
@@ -178,8 +170,8 @@ __device__ __forceinline__ int tile_of_b(const Args &A, uint32_t b, int &bx, int
   }
   return (int)tile;
 }
-template <typename Args>
-__device__ __forceinline__ int tile_of(const Args &A, int &bx, int &by, int &bz, int &s) {
+template <typename T>
+__device__ __forceinline__ int tile_of(const StepArgs<T> &A, int &bx, int &by, int &bz, int &s) {
   return tile_of_b(A, blockIdx.x, bx, by, bz, s);
 }
 
@@ -1074,12 +1066,20 @@ __device__ __forceinline__ Place<T> place_of(const LeapArgs<T> &L) {
 }
 
 // Block -> (64-node tile of x, row, plane, source) and the row's index, for
-// rows of waves: as tile_of with runs of blocks an XCD, without branches.  The
+// rows of waves: as tile_of, but each XCD takes runs of 128 consecutive b,
+// dealt round-robin, and the blocks past the last whole round stay where they
+// are.  Rows of a run still share their neighbours in one L2, and every XCD
+// gets its part of the layers, whose rows cost twice as much: with one
+// contiguous range per XCD the XCDs of the outermost planes finish last (when
+// the runs were introduced: 101x101x61, 4 sources, 53.5 us a step against 47.5
+// with runs and 47.3 unmapped; 1 source 17.5, 17.2 and 19.7; runs of 16 to 1024
+// within 4 %).  The decode has no branches.  The
 // scalar work before a wave's first load was 40 % of an interior wave's
 // instructions, so its limits and divisors come ready from the host (ms before
 // and after: 128x128x96 FP64 9.95 -> 9.65, 200x200x100 with 8 sources 20.9 ->
 // 20.4, 101x101x61 with 4 sources 12.25 -> 12.0, FP32 grids of some 10^4 cells
 // 2 to 12 % less).
+enum { XCD_RUN_LOG2 = 7 };
 template <typename T>
 __device__ __forceinline__ int row_of(const LeapArgs<T> &L, int &bx, int &j, int &k, int &s) {
   constexpr uint32_t g = XCD_RUN_LOG2;
@@ -4397,7 +4397,6 @@ static void enqueue_step(Plan &p, Dev &d, const WS &w, void *vol, bool adj, hipS
       (void)hipEventRecord(ev[0], st);
       (void)hipEventRecord(ev[1], st);
     }
-    const Tiling t = tiling(p);
     launch_leap<T>(p, d, A, vol != nullptr, adj, n, st, ke, keep);
   } else if (p.sched == 1) {
     if (ev) {
