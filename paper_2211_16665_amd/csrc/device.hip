@@ -1039,13 +1039,15 @@ struct LeapArgs {
   // neither a layer nor a wall within the stencil's reach
   uint32_t xs, xn, ys, yn, zs, zn;
   // injections and receivers by row (see build_rows): of each row its receiver
-  // table, of each row and source its source table, or -1 (adjoint runs: null)
+  // table, of each row of the box below and source its source table, or -1
+  // (adjoint runs: null)
   const int *row_tab, *src_tab;
   const int *row_rec;                // [tables][6][64] receiver node of the lane's component, or -1
   const int *row_src;                // [tables][3][64] first coefficient of its injection, or -1
   int rec_mask;                      // components that have receiver nodes at all (Ex .. Hz)
   int adj;                           // adjoint run: the E receiver nodes are the injections
   uint32_t ej, ejn, ek, ekn;         // first and number of the rows and planes they span
+  uint32_t nbx;                      // tiles of a row
 };
 
 // The step a launch computes, from the counter in the workspace, and the
@@ -1106,12 +1108,13 @@ __device__ __forceinline__ void row_kind(const LeapArgs<T> &L, int i0, int j, in
 // ask); n: the step, past the run's last one nothing is injected or recorded
 // (tested last, so that the counter and the tables are in flight together)
 template <typename T>
-__device__ __forceinline__ int2 row_tables(const LeapArgs<T> &L, int b, int j, int k, int s, int n,
-                                           int nt) {
+__device__ __forceinline__ int2 row_tables(const LeapArgs<T> &L, int b, int bx, int j, int k, int s,
+                                           int n, int nt) {
   int2 row = make_int2(-1, -1);
-  if (((uint32_t)j - L.ej < L.ejn) & ((uint32_t)k - L.ek < L.ekn)) {
+  const uint32_t jj = (uint32_t)j - L.ej, kk = (uint32_t)k - L.ek;
+  if ((jj < L.ejn) & (kk < L.ekn)) {
     row.x = L.row_tab[b];
-    if (L.src_tab) row.y = L.src_tab[b * L.ns + s];
+    if (L.src_tab) row.y = L.src_tab[((kk * L.ejn + jj) * L.nbx + bx) * L.ns + s];
   }
   return n < nt ? row : make_int2(-1, -1);
 }
@@ -1449,7 +1452,7 @@ __global__ void __launch_bounds__(64) k_leap(LeapArgs<T> L, StepArgs<T> A) {
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
-  const int2 row = row_tables(L, b, j, k, s, P.n, A.nt);
+  const int2 row = row_tables(L, b, bx, j, k, s, P.n, A.nt);
   if (max(row.x, row.y) >= 0)
     leap_wave<T, HIST, NT, true, true, true>(L, A, P, s, row, i0, j, k);
   else if (xl) {
@@ -1967,7 +1970,7 @@ __global__ void __launch_bounds__(64) k_rows_e4(LeapArgs<T> L, StepArgs<T> A) {
   if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
-  const int2 row = row_tables(L, b, j, k, s, P.n, A.nt);
+  const int2 row = row_tables(L, b, bx, j, k, s, P.n, A.nt);
   if (max(row.x, row.y) >= 0)
     e4_wave<T, HIST, true, true, true>(L, A, P, s, row, i0, j, k);
   else if (xl) {
@@ -3155,7 +3158,7 @@ __global__ void __launch_bounds__(64) k_rows_td_e(LeapArgs<T> L, StepArgs<T> A, 
   row_kind(L, i0, j, k, xl, yz);
   // z: null where no magnetic receiver is recorded
   int2 row = make_int2(-1, -1);
-  if (z) row = row_tables(L, b, j, k, s, 0, 1);
+  if (z) row = row_tables(L, b, bx, j, k, s, 0, 1);
   if (max(row.x, row.y) >= 0)
     td_e_wave<T, true, true, true>(L, A, s, row, i0, j, k, C, z);
   else if (xl) {
@@ -3178,7 +3181,7 @@ __global__ void __launch_bounds__(64) k_rows_td_h(LeapArgs<T> L, StepArgs<T> A, 
   row_kind(L, i0, j, k, xl, yz);
   // z: null at the first step (no sample before it)
   int2 row = make_int2(-1, -1);
-  if (z) row = row_tables(L, b, j, k, s, 0, 1);
+  if (z) row = row_tables(L, b, bx, j, k, s, 0, 1);
   if (max(row.x, row.y) >= 0)
     td_h_wave<T, true, true, true>(L, A, s, row, i0, j, k, Enew, Eold, tdw, C, z);
   else if (xl) {
@@ -3925,53 +3928,63 @@ static V *upload_list(Dev &d, const std::vector<V> &h) {
 // same nodes), and one of the three E components for every row and source
 // with an edge of that source (forward runs; a table a row for all sources
 // would grow with their square).  Also the rows and planes that the entries
-// of either run span (ent_box).
+// of either run span (ent_box); the rows' source tables are listed for the
+// forward run's box alone, as no other row asks (18 MB of -1 on 400x400x200
+// cells with 8 sources otherwise, at every new model).
 static void build_rows(Plan &p, Dev &d) {
   const Tiling t = tiling(p);
   const int nn = (int)p.rn_c.size();
   const int64_t plane = (int64_t)p.NY * p.PX;
-  std::vector<int> tab(t.nblocks, -1), stab((size_t)t.nblocks * p.ns, -1), rec, src;
   for (int m = 0; m < 2; ++m) {
     int *box = d.ent_box[m];
     box[0] = p.NY;
     box[2] = p.NZ;
     box[1] = box[3] = -1;
   }
-  // row (its tile) and lane of a node; run: the runs whose entry it is from
-  auto at = [&](int64_t idx, int run, int &lane) {
+  struct Node {
+    int bx, j, k, lane;
+  };
+  auto at = [&](int64_t idx) {
     const int k = (int)(idx / plane), j = (int)((idx % plane) / p.PX), i = (int)(idx % p.PX);
     if (i >= p.nx || j >= p.ny || k >= p.nz) fail(FWD_ERR_INVALID_ARG, "entry outside the grid");
-    for (int m = 0; m <= run; ++m) {
-      int *box = d.ent_box[m];
-      box[0] = std::min(box[0], j);
-      box[1] = std::max(box[1], j);
-      box[2] = std::min(box[2], k);
-      box[3] = std::max(box[3], k);
-    }
-    lane = i & 63;
-    const int bx = i >> 6;
-    return p.order ? (j * t.nbx + bx) * t.nbz + k : (k * t.nby + j) * t.nbx + bx;
+    return Node{i >> 6, j, k, i & 63};
   };
-  int lane = 0;
+  auto span = [&](int64_t idx, int run) {
+    const Node q = at(idx);
+    int *box = d.ent_box[run];
+    box[0] = std::min(box[0], q.j);
+    box[1] = std::max(box[1], q.j);
+    box[2] = std::min(box[2], q.k);
+    box[3] = std::max(box[3], q.k);
+  };
+  for (int node = 0; node < nn; ++node)
+    for (int run : {0, 1}) span(p.rn_idx[node], run);
+  for (const Target &tg : p.src_tg)
+    if (tg.c < 3) span(tg.idx, 0);            // the others go into H before the step
+  const int *box = d.ent_box[0];
+  const int ejn = std::max(0, box[1] - box[0] + 1), ekn = std::max(0, box[3] - box[2] + 1);
+  std::vector<int> tab(t.nblocks, -1), stab((size_t)ekn * ejn * t.nbx * p.ns, -1), rec, src;
   d.rec_mask = 0;
   for (int node = 0; node < nn; ++node) {
-    int &r = tab[at(p.rn_idx[node], 1, lane)];
+    const Node q = at(p.rn_idx[node]);
+    int &r = tab[p.order ? (q.j * t.nbx + q.bx) * t.nbz + q.k : (q.k * t.nby + q.j) * t.nbx + q.bx];
     if (r < 0) {
       r = (int)(rec.size() / 384);
       rec.resize(rec.size() + 384, -1);
     }
-    rec[((size_t)r * 6 + p.rn_c[node]) * 64 + lane] = node;
+    rec[((size_t)r * 6 + p.rn_c[node]) * 64 + q.lane] = node;
     d.rec_mask |= 1 << p.rn_c[node];
   }
-  for (size_t q = 0; q < p.src_tg.size(); ++q) {
-    const auto &tg = p.src_tg[q];
-    if (tg.c >= 3) continue;                  // into H, before the step or by the H update
-    int &r = stab[(size_t)at(tg.idx, 0, lane) * p.ns + tg.s];
+  for (size_t e = 0; e < p.src_tg.size(); ++e) {
+    const Target &tg = p.src_tg[e];
+    if (tg.c >= 3) continue;
+    const Node q = at(tg.idx);
+    int &r = stab[(((size_t)(q.k - box[2]) * ejn + (q.j - box[0])) * t.nbx + q.bx) * p.ns + tg.s];
     if (r < 0) {
       r = (int)(src.size() / 192);
       src.resize(src.size() + 192, -1);
     }
-    src[((size_t)r * 3 + tg.c) * 64 + lane] = (int)q;
+    src[((size_t)r * 3 + tg.c) * 64 + q.lane] = (int)e;
   }
   d.row_tab = upload_list(d, tab);
   d.src_tab = upload_list(d, stab);
@@ -3986,9 +3999,10 @@ static void build_lists(Plan &p, Dev &d) {
   const bool rows = wave_rows(p);
   if (rows) build_rows(p, d);
   const int nn = (int)p.rn_c.size(), nf = p.nf();
-  for (int mode = rows ? 2 : 0; mode < 4; ++mode) {
+  // the one-launch step has no H update, so no entries of one
+  for (int mode = one_launch(p) ? 4 : rows ? 2 : 0; mode < 4; ++mode) {
     const Tiling t = tiling(p, mode >= 2);   // modes 2 and 3 live on the H update's grid
-    const bool own_h = p.sched != 1 && !one_launch(p);   // the H update adds magnetic sources
+    const bool own_h = p.sched != 1;         // the H update adds magnetic sources
     const int slots = t.bx * t.by;
     struct E {
       int b, slot;
@@ -4319,6 +4333,7 @@ static LeapArgs<T> leap_args(Plan &p, Dev &d, const StepArgs<T> &A, bool vol, bo
   L.ejn = (uint32_t)std::max(0, box[1] - box[0] + 1);
   L.ek = (uint32_t)box[2];
   L.ekn = (uint32_t)std::max(0, box[3] - box[2] + 1);
+  L.nbx = (uint32_t)A.nbx;
   const int D = adj ? 1 : p.dec, m = n + 1, r = m / D & (p.kb - 1);
   const bool hist = vol && m % D == 0 && r != 0;
   if (hist) L.hist = A.hist + (int64_t)(r - 1) * 3 * A.F;
