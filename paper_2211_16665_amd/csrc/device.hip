@@ -1053,7 +1053,12 @@ struct LeapArgs {
 // The step a launch computes, from the counter in the workspace, and the
 // halves that it reads and writes: a captured launch may be replayed, and a
 // plan may step several workspaces in turn, so the host's count decides
-// nothing here.
+// nothing here.  No field can be read before it: its load is kept before the
+// block decode, and nothing that ends a lane stands between them and the
+// variants, so that all arguments come in one wait and the counter's and the
+// rows' tables in the next (ms: 32x32x32 FP64, 512 steps, 2.87 -> 2.82;
+// 101x101x61 gradient 22.39 -> 22.13, with 4 sources 12.23 -> 12.15; with the
+// host's count, which was wrong for those, 2.76, 22.3 and 12.0).
 template <typename T>
 struct Place {
   int n;
@@ -1207,6 +1212,7 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
   // them alive at once)
   asm volatile("; %0" ::"n"(XL * 4 + YZ * 2 + ENT));
   const int tid = threadIdx.x, i = i0 + tid;
+  if (XL && i >= L.nx) return;            // (a row's last tile is of these variants)
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T);
   const bool i_lo = !XL || i >= 1;
@@ -1446,10 +1452,10 @@ __device__ __forceinline__ void leap_wave(const LeapArgs<T> &L, const StepArgs<T
 template <typename T, bool HIST, bool NT>
 __global__ void __launch_bounds__(64) k_leap(LeapArgs<T> L, StepArgs<T> A) {
   const Place<T> P = place_of(L);
+  __builtin_amdgcn_sched_barrier(0);      // see place_of
   int bx, j, k, s;
   const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
-  if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
   const int2 row = row_tables(L, b, bx, j, k, s, P.n, A.nt);
@@ -1667,6 +1673,7 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];   // scalar loads: before the marker
   asm volatile("; h4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));            // see leap_wave
   const int tid = threadIdx.x, i = i0 + tid;
+  if (XL && i >= L.nx) return;            // (a row's last tile is of these variants)
   const int npml = L.npml, W = 2 * npml;
   const uint32_t sz = sizeof(T);
   const uint32_t x0 = (uint32_t)i0 * sz, o = (uint32_t)tid * sz, Fb = L.Fb;
@@ -1805,6 +1812,7 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
   const int n = P.n;
   asm volatile("; e4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));
   const int tid = threadIdx.x, i = i0 + tid;
+  if (XL && i >= L.nx) return;            // (a row's last tile is of these variants)
   RowEnt ent;
   if constexpr (ENT) ent = row_entries(L, A, row, s, tid);
   const int npml = L.npml, W = 2 * npml;
@@ -1944,10 +1952,10 @@ __device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> 
 template <typename T, bool INJ>
 __global__ void __launch_bounds__(64) k_rows_h4(LeapArgs<T> L, StepArgs<T> A) {
   const Place<T> P = place_of(L);
+  __builtin_amdgcn_sched_barrier(0);      // see place_of
   int bx, j, k, s;
   const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
-  if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
   if (INJ && A.tile_tab[b] >= 0)
@@ -1964,10 +1972,10 @@ __global__ void __launch_bounds__(64) k_rows_h4(LeapArgs<T> L, StepArgs<T> A) {
 template <typename T, bool HIST>
 __global__ void __launch_bounds__(64) k_rows_e4(LeapArgs<T> L, StepArgs<T> A) {
   const Place<T> P = place_of(L);
+  __builtin_amdgcn_sched_barrier(0);      // see place_of
   int bx, j, k, s;
   const int b = row_of(L, bx, j, k, s);
   const int i0 = bx * 64;
-  if (i0 + (int)threadIdx.x >= L.nx) return;
   bool xl, yz;
   row_kind(L, i0, j, k, xl, yz);
   const int2 row = row_tables(L, b, bx, j, k, s, P.n, A.nt);
