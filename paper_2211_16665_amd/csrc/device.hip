@@ -923,19 +923,22 @@ k_update_e_s(StepArgs<float> A) {
 // rows, layers and coefficients are scalar; every row is a 32-bit offset on
 // one buffer descriptor (a scalar add a row, 25 rows); the layers' branches
 // cost nothing off the layers; and three quarters of a large grid take the
-// form with none (111 scalar, 92 vector, 56 memory instructions after the
-// block decode).  On 200x200x100 with 8 sources the texture addresser is busy
-// 86 % of the launch (43 % on 101x101x61, where issue bounds): waves of 62 own
-// nodes, whose end lanes carry the neighbours instead of one-lane loads, took
-// 15 % fewer instructions, but their rows leave the 128-byte lines (20.9 ->
-// 24.3 ms there; 12.25 -> 11.4 on 101x101x61 with 4 sources): not kept.
+// form with none.  A wave issues 299 scalar, 233 vector and 66 vector memory
+// instructions on average on 101x101x61 (issue bounds it there) and 229, 158
+// and 56 on 200x200x100 with 8 sources, where the texture addresser is busy
+// 85 % of the launch (41 % on 101x101x61): waves of 62 own nodes, whose end
+// lanes carry the neighbours instead of one-lane loads, took 15 % fewer
+// instructions, but their rows leave the 128-byte lines (20.9 -> 24.3 ms
+// there; 12.25 -> 11.4 on 101x101x61 with 4 sources): not kept.
 // Rows of the high walls are not computed: H there stays zero (it
 // differences E edges on the wall), and E there is never updated.
 //
-// Measured a step, two kernels -> this (one MI355X): 101x101x61 FP32, 30.1 ->
-// 16.9 us; the same with 4 sources 77.2 -> 46.4 us; 200x200x100, 8 sources,
-// 943 -> 610 us (4.0 TB/s of the bytes it cannot do without); FP64
-// 128x128x96 113 -> 82 us.  Not kept: 2 nodes a lane
+// Measured a step, two kernels -> this (one MI355X): 101x101x61 FP32, the
+// kernels alone, with the history sample, 30.1 -> 17.2 us; without a volume, a
+// run's time over its steps: the same grid with 4 sources 77.0 -> 47.5 us,
+// 200x200x100 with 8 sources 967 -> 644 us (2.9 TB/s of the 1.89 GB it cannot
+// do without), 400x400x200 with 8 sources 5.71 -> 4.40 ms; FP64 128x128x96
+// 90.5 -> 63.4 us, 400x400x200 1395 -> 1299 us.  Not kept: 2 nodes a lane
 // (FP32; 20.5 us on the marine grid), a march in z with H of the plane below
 // carried (slower below 32 M node updates a step, 3 % faster above), blocks
 // of 4 rows (5 to 10 % slower than one-wave blocks), holding the layers'
@@ -1058,7 +1061,7 @@ struct LeapArgs {
 // variants, so that all arguments come in one wait and the counter's and the
 // rows' tables in the next (ms: 32x32x32 FP64, 512 steps, 2.87 -> 2.82;
 // 101x101x61 gradient 22.39 -> 22.13, with 4 sources 12.23 -> 12.15; with the
-// host's count, which was wrong for those, 2.76, 22.3 and 12.0).
+// halves chosen by the host, wrong in a replay, 2.76, 22.3 and 12.0).
 template <typename T>
 struct Place {
   int n;
@@ -1659,9 +1662,9 @@ __global__ void __launch_bounds__(256) k_update_e4(StepArgs<T> A) {
 // XL: nodes of the wave may lie in an x layer or within two nodes of an x
 // wall; YZ: the row may lie so in y or z; ENT: it may hold entries.
 // Rows of the high walls are not computed: H there stays zero.
-// Measured (one MI355X, 101x101x61 FP32), general -> rows: H update 14.6 ->
-// 9.6 us, E update 21.0 -> 14.0 us (12.6 without the history sample; its 37 MB
-// take 5 us at the rate of a large copy).
+// Measured (one MI355X, 101x101x61 FP32, the kernels alone), general -> rows: H
+// update 13.1 -> 9.4 us, E update 18.4 -> 12.6 us (11.1 without the history
+// sample; its 37 MB take 5 us at the rate of a large copy).
 template <typename T>
 __device__ __forceinline__ T d4(T a, T b, T c, T d) {
   return fma(T(-1.0 / 24.0), d - a, T(9.0 / 8.0) * (c - b));
@@ -2812,7 +2815,7 @@ __global__ void __launch_bounds__(256) k_td_h(StepArgs<T> A, const T *Enew, cons
 // The same operations in the same order as the general kernels.
 // Multipliers and memory on the high walls stay zero: their rows are skipped.
 // Measured (one MI355X, 101x101x61 FP32), general -> rows: H multipliers 27.3
-// -> 11.8 us, E multipliers and product 35.4 -> 21.3 us (its 94 MB, a third of
+// -> 11.8 us, E multipliers and product 35.4 -> 20.7 us (its 94 MB, a third of
 // them the FP64 sums, take 13 us at the rate of a cached copy), and the two
 // sensitivity launches of 4.8 us a step are gone.
 
@@ -3858,11 +3861,15 @@ struct Tiling {
 // the general kernels where 32-bit byte offsets do not reach (a source's
 // fields, CPML memory or history slot of 4 GB and more) and where magnetic
 // nodes lie on the high walls (the rows of those walls are skipped).
-// The two general kernels on one node per thread are slower on every grid
-// measured (order 2, FP32 us a step: 101x101x61 30.1 against 17.3,
-// 200x200x100 with 4 sources 546 against 381; FP64: 32x32x32 13.3 against
-// 8.2, 128x128x96 113 against 85; order 4, FP32, 101x101x61: 35.6 against
-// 23.6); at order 2 their 16-byte vector forms remain a choice of the caller.
+// The two general kernels on one node per thread, as a plan starts, are slower
+// on every grid measured (us a step; order 2, FP32: 101x101x61 30.1 against
+// 17.2, 200x200x100 with 8 sources 967 against 644, 800x800x60 950 against
+// 642; FP64: 32x32x32 13.4 against 5.5, 128x128x96 90.5 against 63.4,
+// 400x400x200 1395 against 1299; order 4, FP32, 101x101x61: 31.5 against
+// 22.0).  Without the XCD remap, FP64 grids of more than 90,000 nodes a plane
+// ran 2 to 8 % faster on them (400x400x200 1220 against 1320), but their
+// 16-byte vector forms, a choice of the caller and the autotuner's there, are
+// faster than either (1080).
 static bool rows_fit(const Plan &p) {
   const uint64_t lim = (uint64_t)1 << 32;
   return !p.h_on_walls && 6 * (uint64_t)p.field_elems() * p.tsize() < lim &&
