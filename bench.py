@@ -519,7 +519,7 @@ def order4_study(w_true, rho0, order2_s, tsize, accsize):
     nz, ny, nx = plan.shape
     kb = int(plan.get_option(fw.FWD_OPT_DFT_BLOCK))
     kern = kernel_records(ks[:1], 1, nx, ny, nz, w_true.npml, len(w_true.freqs), tsize, accsize,
-                          kb, "F64", max(1, plan.info.nt // kb))
+                          kb, "F64", max(1, plan.info.nt // kb), ("k_rows_h4", "k_rows_e4"))
     nt = plan.info.nt
     out = {"gradient_s": t, "order2_gradient_s": order2_s, "nt": nt, "dt": plan.info.dt,
            "mcell_per_s": 2.0 * nx * ny * nz * nt / t / 1e6,
@@ -646,9 +646,11 @@ def algorithmic_bytes_step(nx, ny, nz, npml, tsize=4, kb=8):
     return int(be - edges * tsize + algorithmic_bytes_h(nx, ny, nz, npml, tsize) - n_e * tsize), edges
 
 
-def kernel_records(stats, ns, nx, ny, nz, npml, nf, tsize, accsize, kb, acc_tag, blocks):
+def kernel_records(stats, ns, nx, ny, nz, npml, nf, tsize, accsize, kb, acc_tag, blocks,
+                   names=("k_update_h", "k_update_e")):
     """Per kernel of a forward step (the one-launch step, or the H update and
-    the E update where the plan runs those; the block transform): the average launch time over the sampled steps of the forward runs in
+    the E update where the plan runs those, ``names``; the block transform):
+    the average launch time over the sampled steps of the forward runs in
     ``stats`` (kernel_stats() results), its algorithmic bytes per launch for
     ``ns`` sources (dt/eps read once for all of them; the transform's
     averaged over the ``blocks`` blocks of a run) and the time per step (the
@@ -659,10 +661,10 @@ def kernel_records(stats, ns, nx, ny, nz, npml, nf, tsize, accsize, kb, acc_tag,
     per_e, edges = algorithmic_bytes_e(nx, ny, nz, npml, tsize, kb, True)
     t = "float" if tsize == 4 else "double"
     out = {
-        "update_h": {"kernel": f"k_update_h<{t}>",
+        "update_h": {"kernel": f"{names[0]}<{t}>",
                      "bytes_per_launch": ns * algorithmic_bytes_h(nx, ny, nz, npml, tsize),
                      "avg_launch_ms": ms[0], "ms_per_step": ms[0]},
-        "update_e": {"kernel": f"k_update_e<{t},hist>",
+        "update_e": {"kernel": f"{names[1]}<{t},hist>",
                      "bytes_per_launch": ns * per_e - (ns - 1) * edges * tsize,
                      "avg_launch_ms": ms[1], "ms_per_step": ms[1]},
         "transform": {"kernel": f"k_transform<{t},{acc_tag},fwd,{kb}>",
