@@ -211,7 +211,10 @@ fwd_status fwd_forward_static(fwd_plan *plan, void *vol_dev, size_t vol_bytes, d
  * returned.  fwd_run_steps advances the state by nsteps (the step index
  * lives in the workspace, so runs may be split anywhere); fwd_run_receivers
  * writes the receiver output of the steps done so far, normalised as in
- * fwd_forward.  Only FWD_MODE_FORWARD runs can be split.  Every call takes
+ * fwd_forward.  Only FWD_MODE_FORWARD runs can be split.  A plan may step
+ * several workspaces in turn: a call with a volume on another workspace than
+ * the plan's last one waits for the stream once, to read its step index (under
+ * stream capture it cannot, and takes the plan's own count).  Every call takes
  * the byte counts of its buffers: a workspace below
  * fwd_workspace_size(FORWARD) or a volume buffer below fwd_volume_size is
  * refused with FWD_ERR_INVALID_ARG before any device work. */

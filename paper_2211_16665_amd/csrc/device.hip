@@ -1671,8 +1671,8 @@ __device__ __forceinline__ T d4(T a, T b, T c, T d) {
 }
 
 template <typename T, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, const Place<T> &P, int s, int b,
-                                        int i0, int j, int k) {
+__device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, const Place<T> &P,
+                                        int s, int b, int i0, int j, int k) {
   const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];   // scalar loads: before the marker
   asm volatile("; h4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));            // see leap_wave
   const int tid = threadIdx.x, i = i0 + tid;
@@ -1809,8 +1809,8 @@ __device__ __forceinline__ void h4_wave(const LeapArgs<T> &L, const StepArgs<T> 
 }
 
 template <typename T, bool HIST, bool XL, bool YZ, bool ENT>
-__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, const Place<T> &P, int s, int2 row,
-                                        int i0, int j, int k) {
+__device__ __forceinline__ void e4_wave(const LeapArgs<T> &L, const StepArgs<T> &A, const Place<T> &P,
+                                        int s, int2 row, int i0, int j, int k) {
   const AxRow<T> yj = L.axr[L.LA + j], zk = L.axr[2 * L.LA + k];
   const int n = P.n;
   asm volatile("; e4 %0" ::"n"(XL * 4 + YZ * 2 + ENT));
@@ -4812,13 +4812,15 @@ static void read_host_step(Plan &p, const void *ws, hipStream_t st) {
 
 // The host's count decides which steps of a run with a volume close a
 // transform block: where it was taken on another workspace (a plan may step
-// several in turn) it is read again.  A stream that is being captured cannot
-// be waited for; there the count stands.
+// several in turn) it is read again.  Steps without a volume need no count, so
+// they wait for nothing and leave it without a workspace.  A stream that is
+// being captured cannot be waited for; there the count stands.
 static void follow_workspace(Plan &p, const void *ws, const void *vol, hipStream_t st) {
-  if (!vol || ws == p.host_ws) return;
+  if (ws == p.host_ws) return;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  HIP_CHECK(hipStreamIsCapturing(st, &cs));
-  if (cs == hipStreamCaptureStatusNone) read_host_step(p, ws, st);
+  if (vol) HIP_CHECK(hipStreamIsCapturing(st, &cs));
+  if (vol && cs == hipStreamCaptureStatusNone) read_host_step(p, ws, st);
+  else p.host_ws = nullptr;
 }
 
 // ---------------------------------------------------------------------------

@@ -168,3 +168,28 @@ def test_volumes_of_two_workspaces(form, between):
     p.run_flush(vb)
     for v in (va, vb):
         assert np.array_equal(p.volume_export(v).cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_volume_beside_a_run_without(form):
+    """Receiver-only steps of another workspace between those of a run with a
+    volume."""
+    p, E = plan(*form)
+    say("a volume beside a run without", form)
+    nt, ref = p.info.nt, p.volume_buffer()
+    p.forward(vol=ref, want_volume=True)
+    a, b, va = buffer(p), buffer(p), p.volume_buffer()
+    p.use_workspace(b)
+    p.run_begin()
+    p.use_workspace(a)
+    p.run_begin(va)
+    for k in (13, 6, nt - 19):
+        p.use_workspace(a)
+        p.run_steps(k, va)
+        p.use_workspace(b)
+        p.run_steps(3)
+    p.run_steps(nt - 9)
+    assert np.array_equal(receivers(p), E)
+    p.use_workspace(a)
+    p.run_flush(va)
+    assert torch.equal(p.volume_export(va), p.volume_export(ref))
